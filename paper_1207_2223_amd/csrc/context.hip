@@ -138,11 +138,18 @@ static wd_status timing_begin(wd_ctx *c, hipEvent_t *e0, hipEvent_t *e1)
     return WD_OK;
 }
 
+static void timing_record(wd_ctx *c, hipEvent_t e1, const char *name, double bytes, double units)
+{
+    (void)hipEventRecord(e1, c->stream);
+    if (c->ev_info.size() < c->ev_used) c->ev_info.resize(c->ev_used);
+    c->ev_info[c->ev_used - 1] = std::make_tuple(std::string(name), bytes, units);
+    c->t_bytes += bytes;
+    c->t_launches++;
+}
+
 // kind: 0 dslash_kernel, 1 dslash_lds_kernel, 2 dslash_tw_kernel
 static void timing_end(wd_ctx *c, const Sweep &sw, hipEvent_t e1, int kind, int nr, int rl, int lk)
 {
-    (void)hipEventRecord(e1, c->stream);
-    const double b = sweep_bytes(c, sw);
     char name[96];
     // the kernel's template instance as profilers print it
     if (kind != 0)
@@ -151,10 +158,7 @@ static void timing_end(wd_ctx *c, const Sweep &sw, hipEvent_t e1, int kind, int 
     else
         snprintf(name, sizeof(name), "dslash_kernel<%d, %d, %d, %d, %s, %d>", sw.sp, lk, nr, rl,
                  sw.dag ? "true" : "false", sw.epi);
-    if (c->ev_info.size() < c->ev_used) c->ev_info.resize(c->ev_used);
-    c->ev_info[c->ev_used - 1] = std::make_tuple(std::string(name), b, (double)c->Vh * sw.nact);
-    c->t_bytes += b;
-    c->t_launches++;
+    timing_record(c, e1, name, sweep_bytes(c, sw), (double)c->Vh * sw.nact);
 }
 
 wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
@@ -261,6 +265,59 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
         return set_error(WD_ERR_HIP, "stencil launch (sp %d lk %d nr %d rl %d epi %d block %d): %s",
                          sw.sp, lk_run, nr, rl, sw.epi, t.block, hipGetErrorString(e));
     if (c->timing) timing_end(c, sw, e1, 0, nr, rl, lk_run);
+    return WD_OK;
+}
+
+// Whether the first sweep of a call reads the caller's field where it lies
+// (its neighbours at 192-byte strides) or a packed copy.  Small lattices are
+// launch-bound and save the pack; FP64 12-real sweeps keep winning (24^3 x 48
+// parity: 95 us against 109, 32^3 x 64: 292 against 338), the others lose
+// where the strided reads stop hitting the caches: FP64 18-real at 24^3 x 24
+// 63 against 70 us, at 24^3 x 48 146 against 135; FP32 at 16^3 x 32 16.0
+// against 18.2, at 24^3 x 24 47 against 34, FP16 alike.
+bool op_reads_canonical(const wd_ctx *c, int sp, int lk, int np, const void *in, const void *out, size_t in_bytes,
+                        size_t out_bytes)
+{
+    // (the output must not overwrite neighbours that other lanes have yet to read)
+    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
+    if (!(a + in_bytes <= b || b + out_bytes <= a)) return false;
+    const long long sites = c->Vh * np;
+    return lk == LK_F64_12 || sites <= (sp == SP_F64 ? 200000 : 65536);
+}
+
+wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs)
+{
+    o.g = c->g;
+    o.links = link_ptr(c, lk);
+    // Links of one right-hand side are streamed once a sweep.  Up to about
+    // the last-level cache a repeated call finds them there and the hint only
+    // hurts (16^3 x 32, 101 MB: Mhat^dag Mhat 68 against 77 us); above it the
+    // hint leaves the L2 to the spinors (24^3 x 48, 254 MB: 372 against 400).
+    const bool nt = (double)c->Vh * o.np * 8.0 * (double)link_bytes(lk) > 180e6;
+    const int block = 64;
+    const long long tiles = (c->Vh + block - 1) / block * o.np;
+    if (tiles > 0x7fffffffLL || nrhs > 65535) return set_error(WD_ERR_ARG, "grid too large");
+    const dim3 grid((unsigned)tiles, (unsigned)nrhs);
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (c->timing) WD_TRY(timing_begin(c, &e0, &e1));
+    hipError_t e = hipErrorInvalidValue;
+    switch (sp) {
+    case SP_F64: e = op_launch_f64(o, lk, nt, dag, grid, block, c->stream); break;
+    case SP_F32: e = op_launch_f32(o, lk, nt, dag, grid, block, c->stream); break;
+    case SP_F16: e = op_launch_f16(o, lk, nt, dag, grid, block, c->stream); break;
+    case SP_I16: e = op_launch_i16(o, lk, nt, dag, grid, block, c->stream); break;
+    }
+    if (e != hipSuccess)
+        return set_error(WD_ERR_HIP, "operator sweep launch (sp %d lk %d): %s", sp, lk, hipGetErrorString(e));
+    if (c->timing) {
+        char name[96];
+        snprintf(name, sizeof(name), "dslash_op_kernel<%d, %d, %s, %s>", sp, lk, dag ? "true" : "false",
+                 o.incanon ? "true" : "false");
+        const double units = (double)c->Vh * o.np * nrhs;
+        const double sb = (double)spinor_site_bytes(sp), io = (o.incanon ? 192.0 : sb) + (o.outcanon ? 192.0 : sb) +
+                          (o.xpay ? (o.xcanon ? 192.0 : sb) : 0.0);
+        timing_record(c, e1, name, (double)c->Vh * o.np * 8.0 * (double)link_bytes(lk) + units * io, units);
+    }
     return WD_OK;
 }
 
@@ -499,39 +556,25 @@ wd_status wd_dslash(wd_ctx *c, double *out, const double *in, int out_parity, in
     WD_TRY(decode_prec(c, prec, &sp, &lk, &xp));
     WD_HIP(hipSetDevice(c->device));
     const int full = (out_parity == WD_FULL);
-    Field fi, fo;
-    WD_TRY(alloc_field(c, "dsl_in", sp, 2, 1, &fi));
-    WD_TRY(alloc_field(c, "dsl_out", sp, 2, 1, &fo));
-    int zero = 0;
-    int *act;
-    WD_TRY(upload_ints(c, "dsl_act", &zero, 1, &act));
-    hipError_t e;
-    if (full) {
-        if ((e = pack_spinor(in, fi, 1, 1, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
-        for (int P = 0; P < 2; P++) {
-            Sweep sw;
-            sw.sp = sp; sw.lk = lk; sw.dag = dagger ? 1 : 0; sw.epi = EPI_PLAIN; sw.P = P;
-            sw.in = sub_view(fi, 1 - P);
-            sw.out = sub_view(fo, P);
-            sw.active = act; sw.nact = 1;
-            WD_TRY(run_sweep(c, sw, nullptr));
-        }
-        if ((e = unpack_spinor(fo, out, 1, 1, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "unpack: %s", hipGetErrorString(e));
+    const size_t bytes = (size_t)(full ? c->V : c->Vh) * 192;
+    OpArgs o;
+    o.full = full;
+    o.np = full ? 2 : 1;
+    o.P0 = out_parity == WD_ODD ? 1 : 0;
+    if (op_reads_canonical(c, sp, lk, o.np, in, out, bytes, bytes)) {
+        o.incanon = 1;
+        o.in = (const char *)in;
     } else {
-        const int P = (out_parity == WD_EVEN) ? 0 : 1;
-        Field vi = sub_view(fi, 0), vo = sub_view(fo, 0);
-        if ((e = pack_spinor(in, vi, 1, 0, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
-        Sweep sw;
-        sw.sp = sp; sw.lk = lk; sw.dag = dagger ? 1 : 0; sw.epi = EPI_PLAIN; sw.P = P;
-        sw.in = vi; sw.out = vo; sw.active = act; sw.nact = 1;
-        WD_TRY(run_sweep(c, sw, nullptr));
-        if ((e = unpack_spinor(vo, out, 1, 0, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "unpack: %s", hipGetErrorString(e));
+        Field f;
+        WD_TRY(alloc_field(c, "dsl_in", sp, full ? 2 : 1, 1, &f));
+        const hipError_t e = pack_spinor(in, f, 1, full, c->g, c->stream);
+        if (e != hipSuccess) return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
+        o.in = f.base;
+        o.in_ss = full ? f.ss : 0;
     }
-    return WD_OK;
+    o.outcanon = 1;
+    o.out = (char *)out;
+    return op_sweep(c, o, sp, lk, dagger ? 1 : 0, 1);
 }
 
 namespace {
@@ -605,57 +648,70 @@ wd_status wd_dslash_shaped(wd_ctx *c, double *out, const double *in, int nrhs, i
 extern "C++" {
 namespace wd {
 
-// M^dag M (eo = 0) or Mhat^dag Mhat (eo = 1) of `in` into `out` (canonical
-// FP64, device) through the packed buffers A, T, B (FP64, two parity
-// subfields each), with dcf = {-kappa, -kappa^2} and act = {0, 1} on the
-// device: the kernels of wd_mdagm and of its allocation-free variant.
-wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, int eo, const double *dcf, const int *act,
-                      const Field &A, const Field &T, const Field &B)
+wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &A, const Field &T,
+                      const Field &B)
 {
-    hipError_t e;
-    Sweep sw;
-    sw.sp = SP_F64; sw.lk = c->lk64; sw.nact = 1;
-    if (eo) {
-        // the coefficient array is indexed by RHS id: use id 1 -> -kappa^2
-        sw.active = act + 1;
-        // fields are addressed as RHS id 1 with zero RHS stride
-        Field a0 = sub_view(A, 0), t1 = sub_view(T, 1), b0 = sub_view(B, 0), c0 = sub_view(T, 0);
-        a0.rs = t1.rs = b0.rs = c0.rs = 0;
-        if ((e = pack_spinor(in, a0, 1, 0, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
-        sw.coef = dcf;
-        sw.P = 1; sw.dag = 0; sw.epi = EPI_PLAIN; sw.in = a0; sw.out = t1;
-        WD_TRY(run_sweep(c, sw, nullptr));
-        sw.P = 0; sw.epi = EPI_XPAY; sw.in = t1; sw.x = a0; sw.out = b0;
-        WD_TRY(run_sweep(c, sw, nullptr));
-        sw.P = 1; sw.dag = 1; sw.epi = EPI_PLAIN; sw.in = b0; sw.out = t1;
-        WD_TRY(run_sweep(c, sw, nullptr));
-        sw.P = 0; sw.epi = EPI_XPAY; sw.in = t1; sw.x = b0; sw.out = c0;
-        WD_TRY(run_sweep(c, sw, nullptr));
-        if ((e = unpack_spinor(c0, out, 1, 0, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "unpack: %s", hipGetErrorString(e));
+    const size_t bytes = (size_t)(eo ? c->Vh : c->V) * 192;
+    // (the last sweep writes out when nothing reads in any more)
+    const bool canon = op_reads_canonical(c, SP_F64, c->lk64, eo ? 1 : 2, in, nullptr, bytes, 0);
+    OpArgs o;
+    if (canon) {
+        o.incanon = 1;
+        o.in = (const char *)in;
     } else {
-        sw.active = act;  // id 0 -> -kappa
-        sw.coef = dcf;
-        if ((e = pack_spinor(in, A, 1, 1, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
-        sw.epi = EPI_XPAY;
-        for (int pass = 0; pass < 2; pass++) {
-            const Field &src = pass ? T : A;
-            const Field &dst = pass ? B : T;
-            sw.dag = pass;
-            for (int P = 0; P < 2; P++) {
-                sw.P = P;
-                sw.in = sub_view(src, 1 - P);
-                sw.x = sub_view(src, P);
-                sw.out = sub_view(dst, P);
-                WD_TRY(run_sweep(c, sw, nullptr));
-            }
-        }
-        if ((e = unpack_spinor(B, out, 1, 1, c->g, c->stream)) != hipSuccess)
-            return set_error(WD_ERR_HIP, "unpack: %s", hipGetErrorString(e));
+        const hipError_t e = pack_spinor(in, A, 1, eo ? 0 : 1, c->g, c->stream);
+        if (e != hipSuccess) return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
+        o.in = A.base;
+        o.in_ss = eo ? 0 : A.ss;
     }
-    return WD_OK;
+    if (eo) {
+        const OpArgs in_e = o;  // the operand on the even sites
+        OpArgs s1 = in_e;       // T = D_oe in
+        s1.P0 = 1;
+        s1.out = T.base;
+        WD_TRY(op_sweep(c, s1, SP_F64, c->lk64, 0, 1));
+        OpArgs s2;              // B = in - k^2 D_eo T
+        s2.in = T.base;
+        s2.xpay = 1;
+        s2.coef = -kappa * kappa;
+        s2.xcanon = in_e.incanon;
+        s2.x = in_e.in;
+        s2.out = B.base;
+        WD_TRY(op_sweep(c, s2, SP_F64, c->lk64, 0, 1));
+        OpArgs s3;              // T = D_oe^dag B
+        s3.P0 = 1;
+        s3.in = B.base;
+        s3.out = T.base;
+        WD_TRY(op_sweep(c, s3, SP_F64, c->lk64, 1, 1));
+        OpArgs s4;              // out = B - k^2 D_eo^dag T
+        s4.in = T.base;
+        s4.xpay = 1;
+        s4.coef = -kappa * kappa;
+        s4.x = B.base;
+        s4.outcanon = 1;
+        s4.out = (char *)out;
+        return op_sweep(c, s4, SP_F64, c->lk64, 1, 1);
+    }
+    o.full = 1;
+    o.np = 2;
+    o.xpay = 1;
+    o.coef = -kappa;
+    OpArgs m = o;  // T = M in
+    m.xcanon = o.incanon;
+    m.x = o.in;
+    m.x_ss = o.in_ss;
+    m.out = T.base;
+    m.out_ss = T.ss;
+    WD_TRY(op_sweep(c, m, SP_F64, c->lk64, 0, 1));
+    OpArgs d = o;  // out = M^dag T
+    d.incanon = 0;
+    d.in = T.base;
+    d.in_ss = T.ss;
+    d.x = T.base;
+    d.x_ss = T.ss;
+    d.outcanon = 1;
+    d.out = (char *)out;
+    return op_sweep(c, d, SP_F64, c->lk64, 1, 1);
 }
 
 }  // namespace wd
@@ -667,17 +723,12 @@ wd_status wd_mdagm(wd_ctx *c, double *out, const double *in, double kappa, int e
     if (!c->have_gauge) return set_error(WD_ERR_STATE, "no gauge field loaded");
     if (!std::isfinite(kappa)) return set_error(WD_ERR_ARG, "kappa not finite");
     WD_HIP(hipSetDevice(c->device));
-    double cf[2] = {-kappa, -kappa * kappa};
-    double *dcf;
-    WD_TRY(upload_doubles(c, "mdm_coef", cf, 2, &dcf));
-    int idx[2] = {0, 1};
-    int *act;
-    WD_TRY(upload_ints(c, "mdm_act", idx, 2, &act));
+    const int nsub = eo ? 1 : 2;
     Field A, T, B;
-    WD_TRY(alloc_field(c, "mdm_a", SP_F64, 2, 1, &A));
-    WD_TRY(alloc_field(c, "mdm_t", SP_F64, 2, 1, &T));
-    WD_TRY(alloc_field(c, "mdm_b", SP_F64, 2, 1, &B));
-    return mdagm_apply(c, out, in, eo, dcf, act, A, T, B);
+    WD_TRY(alloc_field(c, "mdm_a", SP_F64, nsub, 1, &A));
+    WD_TRY(alloc_field(c, "mdm_t", SP_F64, nsub, 1, &T));
+    WD_TRY(alloc_field(c, "mdm_b", SP_F64, nsub, 1, &B));
+    return mdagm_apply(c, out, in, kappa, eo, A, T, B);
 }
 
 wd_status wd_index_tables(const int32_t dims[4], int32_t *nb, int32_t *cb, uint8_t *par)

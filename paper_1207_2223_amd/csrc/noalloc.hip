@@ -2,15 +2,13 @@
 // cannot allocate device memory (code under HIP graph capture, tight serving
 // loops, harnesses that forbid it).
 //
-// The packed operand, the two temporaries of the four stencil sweeps and the
-// two device scalars wd_mdagm keeps in context workspaces live here in one
-// file-scope device array, `scratch`, of kScratchBytes per GPU (held by each
+// The packed operand and the two temporaries of the sweeps that wd_mdagm keeps
+// in context workspaces live here in one file-scope device array, `scratch`, of kScratchBytes per GPU (held by each
 // GPU the library runs on until the process ends).  Its device address is
 // looked up once per device with hipGetSymbolAddress, with that device
 // current, when the first context on that device is created (wd_create), and
 // only that address is handed to kernels.  The entry point itself calls no
-// allocating routine and no host-device copy: the scalars are written by a
-// one-thread kernel.  Every call on one GPU uses that GPU's array, so calls
+// allocating routine and no host-device copy.  Every call on one GPU uses that GPU's array, so calls
 // that overlap on one GPU (different streams or threads) race; the array
 // keeps the last call's contents, and nothing in it is read before this call
 // has written it.
@@ -25,22 +23,12 @@ namespace {
 
 constexpr size_t kScratchBytes = size_t(64) << 20;  // 64 MiB per GPU
 constexpr int kMaxDevices = 64;
-constexpr size_t kScalarBytes = 512;  // {-kappa, -kappa^2} and the id list {0, 1}
+constexpr size_t kHeadBytes = 512;  // before the fields (kept free: part of the size a call is refused by)
 
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 std::mutex g_mu;
 void *g_ptr[kMaxDevices] = {};
-
-__global__ void k_noalloc_scalars(double *coef, int *ids, double c1, double c2)
-{
-    if (threadIdx.x == 0) {
-        coef[0] = c1;
-        coef[1] = c2;
-        ids[0] = 0;
-        ids[1] = 1;
-    }
-}
 
 void *scratch_ptr(int device)
 {
@@ -79,15 +67,13 @@ extern "C" wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, 
     // operator uses both parity subfields of each (6 subfields), the
     // even-odd one subfield of A and B and both of T (4)
     const long long sub = ((long long)spinor_site_bytes(SP_F64) * c->g.cs + 255) / 256 * 256;
-    const size_t need = kScalarBytes + (size_t)((eo ? 4 : 6) * sub);
+    const size_t need = kHeadBytes + (size_t)((eo ? 4 : 6) * sub);
     if (need > kScratchBytes)
         return set_error(WD_ERR_ARG,
                          "the allocation-free M^dag M needs %zu bytes of device scratch on this lattice (Vh = %lld), "
                          "more than its fixed %zu",
                          need, c->Vh, kScratchBytes);
     WD_HIP(hipSetDevice(c->device));
-    double *dcf = (double *)base;
-    int *act = (int *)(base + 256);
     Field f;
     f.sp = SP_F64;
     f.nsub = 2;
@@ -95,15 +81,13 @@ extern "C" wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, 
     f.ss = sub;
     f.rs = 2 * sub;
     Field A = f, T = f, B = f;
-    A.base = base + kScalarBytes;
+    A.base = base + kHeadBytes;
     T.base = A.base + (eo ? 1 : 2) * sub;
     B.base = T.base + 2 * sub;
-    hipLaunchKernelGGL(k_noalloc_scalars, dim3(1), dim3(64), 0, c->stream, dcf, act, -kappa, -kappa * kappa);
-    WD_HIP(hipGetLastError());
     // no per-launch timing events here (event creation allocates)
     const bool timing = c->timing;
     c->timing = false;
-    const wd_status st = mdagm_apply(c, out, in, eo, dcf, act, A, T, B);
+    const wd_status st = mdagm_apply(c, out, in, kappa, eo, A, T, B);
     c->timing = timing;
     return st;
 }

@@ -28,9 +28,10 @@ enum { SP_F64 = 0, SP_F32 = 1, SP_F16 = 2, SP_I16 = 3 };
 // Formats that store a per-site FP32 norm next to 16-bit values.
 __host__ __device__ constexpr bool has_norm(int sp) { return sp == SP_F16 || sp == SP_I16; }
 enum { LK_F64_18 = 0, LK_F64_12 = 1, LK_F32_12 = 2, LK_F16_12 = 3, LK_F32_18 = 4, LK_F32_8 = 5 };
-// FP32 12-real, FP64 12-real and FP32 8-real data read with non-temporal
-// loads (launch variants of the same packed links, not storage formats).
-enum { LK_F32_12N = 6, LK_F64_12N = 7, LK_F32_8N = 8 };
+// FP32 12-real, FP64 12-real, FP32 8-real and FP64 18-real data read with
+// non-temporal loads (launch variants of the same packed links, not storage
+// formats).
+enum { LK_F32_12N = 6, LK_F64_12N = 7, LK_F32_8N = 8, LK_F64_18N = 9 };
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
@@ -262,8 +263,9 @@ template <> struct SpinorIO<SP_F16> {
             for (int j = 0; j < 8; j++) v[8 * k + j] = (T)((float)w[j] * n);
         }
     }
-    template <bool NT = false, typename T>
-    __device__ static __forceinline__ void store(char *f, int cs, int i, const T v[24])
+    // 24 reals to 12 packed pairs; returns the site's norm.
+    template <typename T>
+    __device__ static __forceinline__ float encode(const T v[24], uint32_t w[12])
     {
         // The scaled value is rounded to FP32 and then to FP16 (RNE) by an
         // explicit conversion: left to itself the backend may fuse some of
@@ -272,13 +274,27 @@ template <> struct SpinorIO<SP_F16> {
 #pragma unroll
         for (int j = 0; j < 24; j++) m = fmaxf(m, fabsf((float)v[j]));
         const float inv = (m > 0.f) ? 1.0f / m : 0.f;
+#pragma unroll
+        for (int j = 0; j < 12; j++) w[j] = cvt_pk_f16((float)v[2 * j] * inv, (float)v[2 * j + 1] * inv);
+        return m;
+    }
+    // The two reals of a packed pair with the site norm n, as load gives them.
+    __device__ static __forceinline__ void decode(uint32_t w, float n, float *lo, float *hi)
+    {
+        *lo = (float)__builtin_bit_cast(_Float16, (unsigned short)(w & 0xffffu)) * n;
+        *hi = (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16)) * n;
+    }
+    template <bool NT = false, typename T>
+    __device__ static __forceinline__ void store(char *f, int cs, int i, const T v[24])
+    {
+        uint32_t e[12];
+        const float m = encode(v, e);
         u32x4_t *p = reinterpret_cast<u32x4_t *>(f);
 #pragma unroll
         for (int k = 0; k < 3; k++) {
             u32x4_t w;
 #pragma unroll
-            for (int j = 0; j < 4; j++)
-                w[j] = cvt_pk_f16((float)v[8 * k + 2 * j] * inv, (float)v[8 * k + 2 * j + 1] * inv);
+            for (int j = 0; j < 4; j++) w[j] = e[4 * k + j];
             st_hint<NT>(p + (size_t)k * cs + i, w);
         }
         st_hint<NT>(reinterpret_cast<float *>(f + (size_t)48 * cs) + i, m);
@@ -307,23 +323,39 @@ template <> struct SpinorIO<SP_I16> {
             for (int j = 0; j < 8; j++) v[8 * k + j] = (T)((float)w[j] * sc);
         }
     }
-    template <bool NT = false, typename T>
-    __device__ static __forceinline__ void store(char *f, int cs, int i, const T v[24])
+    // 24 reals to 12 packed pairs; returns the site's norm.
+    template <typename T>
+    __device__ static __forceinline__ float encode(const T v[24], uint32_t w[12])
     {
         float m = 0.f;
 #pragma unroll
         for (int j = 0; j < 24; j++) m = fmaxf(m, fabsf((float)v[j]));
         const float inv = (m > 0.f) ? 32767.0f / m : 0.f;
+#pragma unroll
+        for (int j = 0; j < 12; j++) {
+            const int q0 = min(32767, max(-32767, (int)rintf((float)v[2 * j] * inv)));
+            const int q1 = min(32767, max(-32767, (int)rintf((float)v[2 * j + 1] * inv)));
+            w[j] = ((unsigned)q0 & 0xffffu) | ((unsigned)q1 << 16);
+        }
+        return m;
+    }
+    __device__ static __forceinline__ void decode(uint32_t w, float n, float *lo, float *hi)
+    {
+        const float sc = step(n);
+        *lo = (float)(short)(w & 0xffffu) * sc;
+        *hi = (float)(short)(w >> 16) * sc;
+    }
+    template <bool NT = false, typename T>
+    __device__ static __forceinline__ void store(char *f, int cs, int i, const T v[24])
+    {
+        uint32_t e[12];
+        const float m = encode(v, e);
         u32x4_t *p = reinterpret_cast<u32x4_t *>(f);
 #pragma unroll
         for (int k = 0; k < 3; k++) {
             u32x4_t w;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int q0 = min(32767, max(-32767, (int)rintf((float)v[8 * k + 2 * j] * inv)));
-                const int q1 = min(32767, max(-32767, (int)rintf((float)v[8 * k + 2 * j + 1] * inv)));
-                w[j] = ((unsigned)q0 & 0xffffu) | ((unsigned)q1 << 16);
-            }
+            for (int j = 0; j < 4; j++) w[j] = e[4 * k + j];
             st_hint<NT>(p + (size_t)k * cs + i, w);
         }
         st_hint<NT>(reinterpret_cast<float *>(f + (size_t)48 * cs) + i, m);
@@ -365,21 +397,24 @@ __device__ __forceinline__ void reconstruct_row3(T u[18])
 
 template <int LK> struct LinkIO;
 
-template <> struct LinkIO<LK_F64_18> {
+template <bool NT>
+struct LinkIOF64x18 {
     typedef double real;
     static constexpr int nchunk = 9;
     static constexpr size_t chunk_bytes = 16;
     __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, double u[18])
     {
-        const double2 *p = reinterpret_cast<const double2 *>(U) + (size_t)blk * 9 * cs;
+        const dbl2_t *p = reinterpret_cast<const dbl2_t *>(U) + (size_t)blk * 9 * cs;
 #pragma unroll
         for (int k = 0; k < 9; k++) {
-            double2 w = p[(size_t)k * cs + i];
+            const dbl2_t w = ld_hint<NT>(p + (size_t)k * cs + i);
             u[2 * k] = w.x;
             u[2 * k + 1] = w.y;
         }
     }
 };
+template <> struct LinkIO<LK_F64_18> : LinkIOF64x18<false> {};
+template <> struct LinkIO<LK_F64_18N> : LinkIOF64x18<true> {};
 
 template <bool NT>
 struct LinkIOF64x12 {
@@ -567,12 +602,14 @@ template <> struct LinkIO<LK_F32_8N> : LinkIOF32x8<true> {};
 
 __host__ __device__ constexpr size_t link_bytes(int lk)
 {
-    return lk == LK_F64_18 ? 144
-                           : (lk == LK_F64_12 || lk == LK_F64_12N
-                                  ? 96
-                                  : (lk == LK_F32_12 || lk == LK_F32_12N
-                                         ? 48
-                                         : (lk == LK_F16_12 ? 24 : (lk == LK_F32_8 || lk == LK_F32_8N ? 32 : 72))));
+    switch (lk) {
+    case LK_F64_18: case LK_F64_18N: return 144;
+    case LK_F64_12: case LK_F64_12N: return 96;
+    case LK_F32_12: case LK_F32_12N: return 48;
+    case LK_F16_12: return 24;
+    case LK_F32_8: case LK_F32_8N: return 32;
+    default: return 72;
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -126,6 +126,33 @@ hipError_t dslash_tw_launch(const DslashArgs &a, int sp, int lk, int nr, int dag
                             hipStream_t s);
 bool dslash_tw_supported(int sp, int lk, int nr);
 
+// Operator sweep on canonical fields (dslash_op.h).  A canonical pointer
+// (incanon / xcanon / outcanon) is a complex128 field of one parity, or of
+// the full lattice where full is set, with its RHS stride in doubles; else it
+// is a structure-of-arrays field with byte strides for RHS and parity
+// subfield.
+struct OpArgs {
+    Geom g;
+    int P0 = 0, np = 1;  // output parity, or both (np = 2)
+    int full = 0;        // canonical fields are full-lattice ones (lex order)
+    const char *links = nullptr;
+    int incanon = 0;
+    const char *in = nullptr;
+    long long in_rs = 0, in_ss = 0;  // subfield (1 - P) of in
+    int xpay = 0;                    // FP64: out = x + coef * D in
+    double coef = 0.0;
+    int xcanon = 0;
+    const char *x = nullptr;
+    long long x_rs = 0, x_ss = 0;
+    int outcanon = 0;
+    char *out = nullptr;
+    long long out_rs = 0, out_ss = 0;
+};
+hipError_t op_launch_f64(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_f32(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_f16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_i16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
+
 // BLAS-1 / reductions (blas.hip).  All take an active-RHS list.
 enum { FIN_STORE = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_RR = 3 };
 hipError_t blas_norm(const Field &a, int Vh, const int *active, int nact, double *partial,
@@ -293,8 +320,16 @@ inline int remap_stripes(int remap) { return remap <= 2 || remap >= 5 ? 1 : (rem
 inline int remap_slab_dim(int remap) { return (remap == 5 || remap == 6) ? 3 : 2; }
 const TuneCfg *tuned_cfg(const wd_ctx *c, const Sweep &sw);
 double sweep_bytes(const wd_ctx *c, const Sweep &sw);
-wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, int eo, const double *dcf, const int *act,
-                      const Field &A, const Field &T, const Field &B);
+// One operator sweep of nrhs right-hand sides (g and links are filled in), and
+// whether a call on this lattice reads canonical input in its first sweep.
+wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs);
+bool op_reads_canonical(const wd_ctx *c, int sp, int lk, int np, const void *in, const void *out, size_t in_bytes,
+                        size_t out_bytes);
+// M^dag M or Mhat^dag Mhat of a canonical FP64 field through FP64 buffers of
+// one (eo) or two subfields: A (the packed operand, unless the lattice is read
+// canonically), T and B.
+wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &A, const Field &T,
+                      const Field &B);
 // The allocation-free entry points' device scratch array (noalloc.hip): its
 // address on `device` is looked up once, with that device current (called by
 // wd_create), and kept per device.
