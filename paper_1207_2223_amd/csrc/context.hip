@@ -535,13 +535,14 @@ wd_status wd_gauge_load(wd_ctx *c, const double *U, uint32_t flags)
     WD_TRY(alloc(&c->links32r, n32r));
     WD_TRY(alloc(&c->links8, n8));
     c->lk64 = lk64;
-    hipError_t e;
-    if ((e = pack_gauge(U, c->links64, lk64, c->g, c->stream)) != hipSuccess ||
-        (e = pack_gauge(U, c->links32, LK_F32_12, c->g, c->stream)) != hipSuccess ||
-        (e = pack_gauge(U, c->links16, LK_F16_12, c->g, c->stream)) != hipSuccess ||
-        (e = pack_gauge(U, c->links32r, LK_F32_18, c->g, c->stream)) != hipSuccess ||
-        (e = pack_gauge(U, c->links8, LK_F32_8, c->g, c->stream)) != hipSuccess)
-        return set_error(WD_ERR_HIP, "gauge packing failed: %s", hipGetErrorString(e));
+    LinkDst d;
+    d.f64 = c->links64;
+    d.f32 = c->links32;
+    d.f32r = c->links32r;
+    d.f8 = c->links8;
+    d.f16 = c->links16;
+    const hipError_t e = pack_gauge(U, d, lk64, c->g, c->stream);
+    if (e != hipSuccess) return set_error(WD_ERR_HIP, "gauge packing failed: %s", hipGetErrorString(e));
     c->have_gauge = true;
     return WD_OK;
 }

@@ -25,30 +25,89 @@ __device__ __forceinline__ void lex_to_eo(const Geom &g, long long lex, int *P, 
     *cb = (int)(lex >> 1);
 }
 
-// links: one thread per (lex, mu)
-template <int LK>
-__global__ void __launch_bounds__(kBlock) k_pack_gauge(const double *U, char *dst, Geom g)
+// A complex number of the caller's field (only the alignment of doubles is
+// taken for granted).
+typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
+
+// Links: all the packed formats in one pass over the canonical field.  A
+// work-group stages 64 consecutive sites (36 KB, read as they lie) in LDS;
+// wave mu then takes direction mu, its lanes 0-31 the even and 32-63 the odd
+// sites, so that a half wave writes 32 consecutive slots of one (parity, mu)
+// block in every format.  Bound by memory: U is read once and each format
+// written once (464 bytes a link with FP64 18-real links).  One kernel per
+// format read U five times with lanes 144 bytes apart: 24^3 x 48 with FP64
+// 12-real links 706 us against 205 now (1.1 GB, 5.4 TB/s), 32^3 x 64 with
+// 18-real ones 2.42 ms against 0.75.  The site stride of 592 bytes in LDS
+// keeps the 16-byte reads of 8 lanes on different banks (576 would put them
+// all on one).
+constexpr int kPackSites = 64;
+constexpr int kPackStride = 37;  // 16-byte words of a staged site: 36 and one of padding
+
+template <int LK64>
+__global__ void __launch_bounds__(kBlock) k_pack_gauge(const double *U, LinkDst dst, Geom g)
 {
-    const long long V = 2LL * g.Vh;
-    const long long idx = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= 4 * V) return;
-    const long long lex = idx >> 2;
-    const int mu = (int)(idx & 3);
-    int P, cb;
-    lex_to_eo(g, lex, &P, &cb);
-    const double *u = U + idx * 18;
+    __shared__ dbl2_t st[kPackSites * kPackStride];
+    const long long s0 = (long long)blockIdx.x * kPackSites, V = 2LL * g.Vh;
+    const dbl2u_t *src = reinterpret_cast<const dbl2u_t *>(U) + s0 * 36;
+    const int words = (int)(V - s0 < kPackSites ? V - s0 : kPackSites) * 36;
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const int w = k * kBlock + (int)threadIdx.x;
+        if (w < words) {
+            const int site = w / 36;
+            st[site * kPackStride + (w - site * 36)] = src[w];
+        }
+    }
+    __syncthreads();
+    const int mu = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, P = lane >> 5;
+    const int cb = (int)(s0 >> 1) + (lane & 31);
+    if (cb >= g.Vh) return;
+    int c[4];
+    site_coords(g, cb, P, c);
+    double u[18];
+    {
+        const dbl2_t *q = st + (2 * (lane & 31) + (c[0] & 1)) * kPackStride + mu * 9;
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            u[2 * k] = q[k].x;
+            u[2 * k + 1] = q[k].y;
+        }
+    }
     const int blk = P * 4 + mu;
     const size_t cs = g.cs;
-    if (LK == LK_F64_18 || LK == LK_F64_12) {
-        const int nch = (LK == LK_F64_18) ? 9 : 6;
-        double2 *d = reinterpret_cast<double2 *>(dst) + (size_t)blk * nch * cs;
+    if (dst.f64) {
+        constexpr int nch = (LK64 == LK_F64_18) ? 9 : 6;
+        double2 *d = reinterpret_cast<double2 *>(dst.f64) + (size_t)blk * nch * cs;
+#pragma unroll
         for (int k = 0; k < nch; k++) d[k * cs + cb] = make_double2(u[2 * k], u[2 * k + 1]);
-    } else if (LK == LK_F32_12) {
-        float4 *d = reinterpret_cast<float4 *>(dst) + (size_t)blk * 3 * cs;
+    }
+    if (dst.f32) {
+        float4 *d = reinterpret_cast<float4 *>(dst.f32) + (size_t)blk * 3 * cs;
+#pragma unroll
         for (int k = 0; k < 3; k++)
             d[k * cs + cb] = make_float4((float)u[4 * k], (float)u[4 * k + 1], (float)u[4 * k + 2],
                                          (float)u[4 * k + 3]);
-    } else if (LK == LK_F32_8) {
+    }
+    if (dst.f32r) {
+        float4 *d = reinterpret_cast<float4 *>(dst.f32r) + (size_t)blk * 4 * cs;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            d[k * cs + cb] = make_float4((float)u[4 * k], (float)u[4 * k + 1], (float)u[4 * k + 2],
+                                         (float)u[4 * k + 3]);
+        float2 *q = reinterpret_cast<float2 *>(reinterpret_cast<float4 *>(dst.f32r) + 32 * cs) + (size_t)blk * cs;
+        q[cb] = make_float2((float)u[16], (float)u[17]);
+    }
+    if (dst.f16) {
+        half4_t *d = reinterpret_cast<half4_t *>(dst.f16) + (size_t)blk * 3 * cs;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            half4_t w;
+#pragma unroll
+            for (int j = 0; j < 4; j++) w[j] = (_Float16)u[4 * k + j];
+            d[k * cs + cb] = w;
+        }
+    }
+    if (dst.f8) {
         // U' = s P C_k(U) (see LinkIO<LK_F32_8>): k takes the largest entry
         // of row 1 to U'_11; P swaps rows 2 and 3 (and s = -1) when |U'_31| <
         // |U'_21|; a block-diagonal U' keeps its lower block's first row
@@ -56,10 +115,12 @@ __global__ void __launch_bounds__(kBlock) k_pack_gauge(const double *U, char *ds
         for (int j = 0; j < 3; j++) m[j] = u[2 * j] * u[2 * j] + u[2 * j + 1] * u[2 * j + 1];
         const int k = (m[1] > m[0] && m[1] >= m[2]) ? 1 : ((m[2] > m[0] && m[2] > m[1]) ? 2 : 0);
         double v[18];
+#pragma unroll
         for (int row = 0; row < 3; row++)
-            for (int j = 0; j < 3; j++) {
-                v[6 * row + 2 * j] = u[6 * row + 2 * ((j + k) % 3)];
-                v[6 * row + 2 * j + 1] = u[6 * row + 2 * ((j + k) % 3) + 1];
+#pragma unroll
+            for (int e = 0; e < 6; e++) {  // (selects: an indexed register file would go to scratch)
+                const double x0 = u[6 * row + e], x1 = u[6 * row + (e + 2) % 6], x2 = u[6 * row + (e + 4) % 6];
+                v[6 * row + e] = k == 0 ? x0 : (k == 1 ? x1 : x2);
             }
         const double N = v[2] * v[2] + v[3] * v[3] + v[4] * v[4] + v[5] * v[5];
         const bool deg = !(N >= 1e-30);
@@ -76,26 +137,12 @@ __global__ void __launch_bounds__(kBlock) k_pack_gauge(const double *U, char *ds
         const float pa = __uint_as_float((__float_as_uint((float)(atan2(v[1], v[0]) * inv2pi)) & ~3u) | (unsigned)k);
         const float pc = __uint_as_float((__float_as_uint(deg ? 0.0f : (float)(atan2(v[13], v[12]) * inv2pi)) & ~3u) |
                                          (swp ? 1u : 0u) | (deg ? 2u : 0u));
-        float4 *d = reinterpret_cast<float4 *>(dst) + (size_t)blk * 2 * cs;
+        float4 *d = reinterpret_cast<float4 *>(dst.f8) + (size_t)blk * 2 * cs;
         if (deg)
             d[cb] = make_float4((float)v[8], (float)v[9], (float)v[10], (float)v[11]);
         else
             d[cb] = make_float4((float)v[2], (float)v[3], (float)v[4], (float)v[5]);
         d[cs + cb] = make_float4(deg ? 0.0f : (float)v[6], deg ? 0.0f : (float)v[7], pa, pc);
-    } else if (LK == LK_F32_18) {
-        float4 *d = reinterpret_cast<float4 *>(dst) + (size_t)blk * 4 * cs;
-        for (int k = 0; k < 4; k++)
-            d[k * cs + cb] = make_float4((float)u[4 * k], (float)u[4 * k + 1], (float)u[4 * k + 2],
-                                         (float)u[4 * k + 3]);
-        float2 *q = reinterpret_cast<float2 *>(reinterpret_cast<float4 *>(dst) + 32 * cs) + (size_t)blk * cs;
-        q[cb] = make_float2((float)u[16], (float)u[17]);
-    } else {
-        half4_t *d = reinterpret_cast<half4_t *>(dst) + (size_t)blk * 3 * cs;
-        for (int k = 0; k < 3; k++) {
-            half4_t w;
-            for (int j = 0; j < 4; j++) w[j] = (_Float16)u[4 * k + j];
-            d[k * cs + cb] = w;
-        }
     }
 }
 
@@ -171,19 +218,14 @@ __global__ void __launch_bounds__(kBlock) k_debug_tables(Geom g, int32_t *nb, in
 
 }  // namespace
 
-hipError_t pack_gauge(const double *U, char *dst, int lk, const Geom &g, hipStream_t s)
+hipError_t pack_gauge(const double *U, const LinkDst &dst, int lk64, const Geom &g, hipStream_t s)
 {
-    const long long n = 8LL * g.Vh;  // 4 V links
-    dim3 gr((unsigned)((n + kBlock - 1) / kBlock));
-    switch (lk) {
-    case LK_F64_18: hipLaunchKernelGGL(k_pack_gauge<LK_F64_18>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    case LK_F64_12: hipLaunchKernelGGL(k_pack_gauge<LK_F64_12>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    case LK_F32_12: hipLaunchKernelGGL(k_pack_gauge<LK_F32_12>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    case LK_F16_12: hipLaunchKernelGGL(k_pack_gauge<LK_F16_12>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    case LK_F32_18: hipLaunchKernelGGL(k_pack_gauge<LK_F32_18>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    case LK_F32_8: hipLaunchKernelGGL(k_pack_gauge<LK_F32_8>, gr, dim3(kBlock), 0, s, U, dst, g); break;
-    default: return hipErrorInvalidValue;
-    }
+    const long long V = 2LL * g.Vh;
+    dim3 gr((unsigned)((V + kPackSites - 1) / kPackSites));
+    if (lk64 == LK_F64_18)
+        hipLaunchKernelGGL(k_pack_gauge<LK_F64_18>, gr, dim3(kBlock), 0, s, U, dst, g);
+    else
+        hipLaunchKernelGGL(k_pack_gauge<LK_F64_12>, gr, dim3(kBlock), 0, s, U, dst, g);
     return hipGetLastError();
 }
 

@@ -193,7 +193,12 @@ hipError_t blas_finalize(const double *partial, int pstride, int nw, const int *
 inline int ngroups_of(int nsites) { return (nsites + 15) / 16; }
 
 // Packing between the canonical complex128 layouts and the internal ones (pack.hip).
-hipError_t pack_gauge(const double *U, char *dst, int lk, const Geom &g, hipStream_t s);
+// The packed copies of the links to write (null: not this one): FP64 (18- or
+// 12-real, lk64), FP32 12-real, FP32 18-real, FP32 8-real, FP16 12-real.
+struct LinkDst {
+    char *f64 = nullptr, *f32 = nullptr, *f32r = nullptr, *f8 = nullptr, *f16 = nullptr;
+};
+hipError_t pack_gauge(const double *U, const LinkDst &dst, int lk64, const Geom &g, hipStream_t s);
 // mode 0: src/dst are parity fields ([Vh][4][3] cb order <-> one subfield);
 // mode 1: full fields ([V][4][3] lex order <-> two subfields).
 hipError_t pack_spinor(const double *src, const Field &dst, int nrhs, int mode, const Geom &g,

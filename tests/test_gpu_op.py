@@ -11,6 +11,10 @@ from gpu_util import dev, empty_like_dev, host, note, rel_err
 
 pytestmark = pytest.mark.gpu
 
+# the relative 2-norm bounds of tests/test_gpu_dslash.py (the packed links of the
+# last, partial work-group of the packing kernel are among those read here)
+TOL = {"f64": 1e-12, "f32": 2e-7, "f32l16": 4.5e-4, "f32r18": 2e-7, "f32r8": 6e-7, "f16": 6e-4, "f16l16": 9e-4,
+       "f16r18": 6e-4, "f16r8": 6e-4, "i16": 6e-5, "i16l16": 4.5e-4}
 CODES = {"f64": 0, "f32": 1, "f32l16": 1 | 0x10, "f32r18": 1 | 0x20, "f32r8": 1 | 0x40, "f16": 2, "f16l16": 2 | 0x10,
          "f16r18": 2 | 0x20, "f16r8": 2 | 0x40, "i16": 3, "i16l16": 3 | 0x10}
 
@@ -48,10 +52,9 @@ def test_canonical_and_packed_input_give_the_same_bits(wd, oracle, prec, dims):
                     shaped = empty_like_dev(psi)
                     wd.wd_dslash_shaped(lat.ctx, shaped, dev(psi), part, dag, CODES[prec])
                     assert np.array_equal(bits(out), bits(shaped))
-                if prec == "f64":  # FP64 rounding of 8 x 12 products
-                    ref = oracle.hop(dims, U, psi, dagger=bool(dag)) if part == wd.WD_FULL else oracle.hop_eo(
-                        dims, U, psi, 1 if part == wd.WD_ODD else 0, dagger=bool(dag))
-                    assert rel_err(host(out), ref) <= 1e-12
+                ref = oracle.hop(dims, U, psi, dagger=bool(dag)) if part == wd.WD_FULL else oracle.hop_eo(
+                    dims, U, psi, 1 if part == wd.WD_ODD else 0, dagger=bool(dag))
+                assert rel_err(host(out), ref) <= TOL[prec]
         lat.close()
 
 
