@@ -24,6 +24,7 @@
 #include <cmath>
 #include <vector>
 
+#include "m3.h"
 #include "wd_internal.h"
 
 namespace wd {
@@ -73,56 +74,10 @@ __host__ __device__ inline void normals(uint64_t seed, uint32_t site, uint32_t t
     *n2 = rad * sin(th);
 }
 
-// ----- 3x3 complex matrices (row-major double2) -----
-struct M3 {
-    double2 e[9];
-};
-
-__device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 __device__ inline double2 cmulc(double2 a, double2 b)  // a * conj(b)
 {
     return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
-__device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-
-__device__ inline M3 load_m3(const double *p)
-{
-    M3 m;
-    const double2 *q = reinterpret_cast<const double2 *>(p);
-#pragma unroll
-    for (int k = 0; k < 9; k++) m.e[k] = q[k];
-    return m;
-}
-__device__ inline void store_m3(double *p, const M3 &m)
-{
-    double2 *q = reinterpret_cast<double2 *>(p);
-#pragma unroll
-    for (int k = 0; k < 9; k++) q[k] = m.e[k];
-}
-__device__ inline M3 mul(const M3 &a, const M3 &b)
-{
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            double2 s = cmul(a.e[3 * i], b.e[j]);
-            s = cadd(s, cmul(a.e[3 * i + 1], b.e[3 + j]));
-            s = cadd(s, cmul(a.e[3 * i + 2], b.e[6 + j]));
-            c.e[3 * i + j] = s;
-        }
-    return c;
-}
-__device__ inline M3 dagger(const M3 &a)
-{
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) c.e[3 * i + j] = make_double2(a.e[3 * j + i].x, -a.e[3 * j + i].y);
-    return c;
-}
-__device__ inline M3 mul_dag(const M3 &a, const M3 &b) { return mul(a, dagger(b)); }
 // traceless Hermitian part (W - W^dag)/(2i) - tr/3
 __device__ inline M3 ta_herm(const M3 &w)
 {
@@ -209,33 +164,75 @@ __global__ void __launch_bounds__(kB) k_draw_chi(double *chi, int nsites, uint64
     }
 }
 
-// F = (beta/3) TA[U_mu(x) A_mu(x)], A = sum of the six staples
+// F = (beta/3) TA[U_mu(x) A_mu(x)], A = sum of the six staples.  Three lanes
+// a link, one row each (see stage_links): a lane's row of U times each staple
+// in turn is its row of U A, and the rows meet in LDS for the traceless part.
+// Each XCD takes a contiguous range of sites.  16^3 x 32 (75 MB of links in,
+// 75 MB out) 174 us with one lane a link reading its own links in dispatch
+// order, 133 now.
 __global__ void __launch_bounds__(kB) k_gauge_force(const double *U, double *F, Geom g, double beta)
 {
-    const int l = blockIdx.x * kB + threadIdx.x;
-    if (l >= 8 * g.Vh) return;
-    const int x = l >> 2, mu = l & 3;
+    __shared__ dbl2_t sh[kB / 64][kRowWords];
+    const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    dbl2_t *lds = sh[w];
+    const int nl = 8 * g.Vh;
+    const int l0 = (xcd_remap((int)blockIdx.x, (int)gridDim.x) * (kB / 64) + w) * kRowLinks + lane / 3;
+    const int l = l0 < nl ? l0 : nl - 1;
+    const int x = l >> 2, mu = l & 3, row = lane % 3;
     int c[4];
     coords_lex(g, x, c);
-    M3 A;
-    for (int k = 0; k < 9; k++) A.e[k] = make_double2(0, 0);
     const int xm = shift(g, c, mu, +1);
-    for (int nu = 0; nu < 4; nu++) {
-        if (nu == mu) continue;
+    stage_links(fetch_links(U, l), lds);
+    const Row3 u = staged_row(lds);
+    Row3 W;
+#pragma unroll
+    for (int k = 0; k < 3; k++) W.e[k] = make_double2(0, 0);
+#pragma unroll 1
+    for (int d = 1; d < 4; d++) {
+        const int nu = (mu + d) & 3;
         const int xn = shift(g, c, nu, +1), xbn = shift(g, c, nu, -1);
         const int xmbn = shift2(g, c, mu, +1, nu, -1);
         // upper: U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-        M3 t = mul_dag(load_m3(lk(U, xm, nu)), load_m3(lk(U, xn, mu)));
-        t = mul_dag(t, load_m3(lk(U, x, nu)));
+        const LinkWords f1 = fetch_links(U, xm * 4 + nu), f2 = fetch_links(U, xn * 4 + mu),
+                        f3 = fetch_links(U, x * 4 + nu);
+        stage_links(f1, lds);
+        Row3 t = row_mul(u, lds);
+        stage_links(f2, lds);
+        t = row_mul_dag(t, lds);
+        stage_links(f3, lds);
+        t = row_mul_dag(t, lds);
+#pragma unroll
+        for (int k = 0; k < 3; k++) W.e[k] = cadd(W.e[k], t.e[k]);
         // lower: U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-        M3 b = mul(dagger(load_m3(lk(U, xmbn, nu))), dagger(load_m3(lk(U, xbn, mu))));
-        b = mul(b, load_m3(lk(U, xbn, nu)));
-        for (int k = 0; k < 9; k++) A.e[k] = cadd(A.e[k], cadd(t.e[k], b.e[k]));
+        __builtin_amdgcn_sched_barrier(0);
+        const LinkWords f4 = fetch_links(U, xmbn * 4 + nu), f5 = fetch_links(U, xbn * 4 + mu),
+                        f6 = fetch_links(U, xbn * 4 + nu);
+        stage_links(f4, lds);
+        t = row_mul_dag(u, lds);
+        stage_links(f5, lds);
+        t = row_mul_dag(t, lds);
+        stage_links(f6, lds);
+        t = row_mul(t, lds);
+#pragma unroll
+        for (int k = 0; k < 3; k++) W.e[k] = cadd(W.e[k], t.e[k]);
     }
-    M3 f = ta_herm(mul(load_m3(lk(U, x, mu)), A));
-    const double sc = beta / 3.0;
-    for (int k = 0; k < 9; k++) f.e[k] = make_double2(sc * f.e[k].x, sc * f.e[k].y);
-    store_m3(F + (size_t)l * 18, f);
+    // the rows of W to LDS; then each lane its row of (W - W^dag)/(2i) - tr/3
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < 3; k++) lds[lane * 3 + k] = dbl2_t{W.e[k].x, W.e[k].y};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const dbl2_t *m = lds + lane / 3 * 9;
+    const double tr = (m[0].y + m[4].y + m[8].y) / 3.0, sc = beta / 3.0;
+    if (lane >= 3 * kRowLinks || l0 >= nl) return;
+    dbl2u_t *f = reinterpret_cast<dbl2u_t *>(F + (size_t)l * 18 + 6 * row);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const dbl2_t b = m[3 * k + row];
+        const double re = 0.5 * (W.e[k].y + b.y) - (k == row ? tr : 0.0), im = -0.5 * (W.e[k].x - b.x);
+        f[k] = dbl2u_t{sc * re, sc * im};
+    }
 }
 
 // [(1 + S g_mu) psi] as a full 4-spinor (v: 24 reals) from the projection rules
@@ -366,25 +363,54 @@ __device__ inline void put_partial(double v, double *partial, int idx, bool live
     if ((threadIdx.x & 15) == 0 && live) partial[idx >> 4] = v;
 }
 
-// per site: sum_{mu<nu} Re tr U_munu / 3
+// Sum over the sites of a work-group of sum_{mu<nu} Re tr U_munu / 3, as Re
+// sum_ij (U_mu(x) U_nu(x+mu))_ij conj((U_nu(x) U_mu(x+nu))_ij).  Three lanes
+// a site, one row each (see stage_links); each XCD takes a contiguous range of
+// sites, so that neighbours in y and z are read through one L2.  24^3 x 48
+// (382 MB of links) 416 us with one lane a site reading its own links in
+// dispatch order, 235 now; what remains is the t neighbours, a slice of 8 MB
+// away, past the L2, and the LDS reads.
+constexpr int kPlaqSites = kB / 64 * kRowLinks;
 __global__ void __launch_bounds__(kB) k_plaq(const double *U, Geom g, double *partial)
 {
-    const int x = blockIdx.x * kB + threadIdx.x;
-    const int V = 2 * g.Vh;
+    __shared__ dbl2_t sh[kB / 64][kRowWords];
+    __shared__ double tot[kB / 64];
+    const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    dbl2_t *lds = sh[w];
+    const int V = 2 * g.Vh, blk = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+    const int x0 = (blk * (kB / 64) + w) * kRowLinks + lane / 3;
+    const bool live = lane < 3 * kRowLinks && x0 < V;
+    const int x = x0 < V ? x0 : V - 1;
+    int c[4];
+    coords_lex(g, x, c);
     double s = 0;
-    if (x < V) {
-        int c[4];
-        coords_lex(g, x, c);
-        for (int mu = 0; mu < 4; mu++)
-            for (int nu = mu + 1; nu < 4; nu++) {
-                const int xm = shift(g, c, mu, +1), xn = shift(g, c, nu, +1);
-                M3 t = mul(load_m3(lk(U, x, mu)), load_m3(lk(U, xm, nu)));
-                t = mul_dag(t, load_m3(lk(U, xn, mu)));
-                t = mul_dag(t, load_m3(lk(U, x, nu)));
-                s += (t.e[0].x + t.e[4].x + t.e[8].x) / 3.0;
-            }
+#pragma unroll 1
+    for (int mu = 0; mu < 3; mu++) {
+        stage_links(fetch_links(U, x * 4 + mu), lds);
+        const Row3 um = staged_row(lds);
+        const int xm = shift(g, c, mu, +1);
+#pragma unroll 1
+        for (int nu = mu + 1; nu < 4; nu++) {
+            const LinkWords f1 = fetch_links(U, xm * 4 + nu), f2 = fetch_links(U, x * 4 + nu),
+                            f3 = fetch_links(U, shift(g, c, nu, +1) * 4 + mu);
+            stage_links(f1, lds);
+            const Row3 a = row_mul(um, lds);
+            stage_links(f2, lds);
+            const Row3 un = staged_row(lds);
+            stage_links(f3, lds);
+            const Row3 b = row_mul(un, lds);
+            double t = 0;
+#pragma unroll
+            for (int k = 0; k < 3; k++) t = fmaT(a.e[k].x, b.e[k].x, fmaT(a.e[k].y, b.e[k].y, t));
+            s += t / 3.0;
+        }
     }
-    put_partial(s, partial, x, x < V);
+    if (!live) s = 0;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) tot[w] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[blk] = (tot[0] + tot[1]) + (tot[2] + tot[3]);
 }
 
 // per element: sum of a[i] * b[i] (a real dot of two double arrays)
@@ -497,10 +523,11 @@ wd_status dot_host(wd_ctx *c, HmcWs &w, const double *a, const double *b, long l
 wd_status plaquette_host(wd_ctx *c, HmcWs &w, const double *U, double *plaq)
 {
     const int V = (int)c->V;
-    hipLaunchKernelGGL(k_plaq, dim3(nblk(V)), dim3(kB), 0, c->stream, U, c->g, w.partial);
+    const int nb = (V + kPlaqSites - 1) / kPlaqSites;
+    hipLaunchKernelGGL(k_plaq, dim3(nb), dim3(kB), 0, c->stream, U, c->g, w.partial);
     HIPCHK(hipGetLastError());
     double s;
-    WD_TRY(finish_sum(c, w, (V + 15) / 16, &s));
+    WD_TRY(finish_sum(c, w, nb, &s));
     *plaq = s / (6.0 * V);
     return WD_OK;
 }
@@ -542,7 +569,7 @@ wd_status md_force(wd_ctx *c, HmcWs &w, double beta, double kappa, const wd_solv
                    int *iters)
 {
     const int nl = 8 * (int)c->Vh;
-    hipLaunchKernelGGL(k_gauge_force, dim3(nblk(nl)), dim3(kB), 0, c->stream, w.U, w.F, c->g, beta);
+    hipLaunchKernelGGL(k_gauge_force, dim3((unsigned)((nl + kPlaqSites - 1) / kPlaqSites)), dim3(kB), 0, c->stream, w.U, w.F, c->g, beta);
     HIPCHK(hipGetLastError());
     wd_solver_stats st;
     wd_status s = wd_cg_solve(c, w.Xe, w.phi, 1, &kappa, sp, &st);

@@ -17,6 +17,7 @@
 #include <cstring>
 #include <vector>
 
+#include "m3.h"
 #include "wd_internal.h"
 
 namespace wd {
@@ -127,71 +128,81 @@ __global__ void k_corr_final(const double *partial, int nb, int Lt, int t0, doub
     out[dt] = s;
 }
 
-struct C3 {
-    double2 e[9];
-};
-
-__device__ inline C3 load3(const double *p)
+// Per spatial site s: (1/3) tr prod_{t = 0..Lt-1} U_t(s, t).  A work-group
+// takes kRowLinks sites, three lanes a site; each of its kPolySeg waves
+// multiplies the links of a contiguous range of t, and the first wave
+// multiplies the ranges in order.  partial[2 * b + {0, 1}]: (Re, Im) summed
+// over the sites.  A chain of Lt dependent products per thread over v3 threads
+// left most of the chip idle: 24^3 x 48 101 us, 28 now.
+constexpr int kPolySeg = 8;
+__global__ void __launch_bounds__(64 * kPolySeg) k_poly_partial(const double *U, int v3, int Lt, double *partial)
 {
-    C3 m;
+    __shared__ dbl2_t sh[kPolySeg][kRowWords];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane % 3;
+    dbl2_t *lds = sh[w];
+    const int s0 = blockIdx.x * kRowLinks + lane / 3;
+    const int s = s0 < v3 ? s0 : v3 - 1;
+    Row3 P;
 #pragma unroll
-    for (int k = 0; k < 9; k++) m.e[k] = make_double2(p[2 * k], p[2 * k + 1]);
-    return m;
-}
-
-__device__ inline C3 mul3(const C3 &a, const C3 &b)
-{
-    C3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            double re = 0.0, im = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const double2 x = a.e[3 * i + k], y = b.e[3 * k + j];
-                re = fmaT(x.x, y.x, re);
-                re = fmaT(-x.y, y.y, re);
-                im = fmaT(x.x, y.y, im);
-                im = fmaT(x.y, y.x, im);
-            }
-            c.e[3 * i + j] = make_double2(re, im);
+    for (int k = 0; k < 3; k++) P.e[k] = make_double2(k == row ? 1.0 : 0.0, 0.0);
+    const int t1 = Lt * (w + 1) / kPolySeg;
+#pragma unroll 1
+    for (int t = Lt * w / kPolySeg; t < t1; t += 3) {
+        // three links in flight; those past the range are fetched but not used
+        const LinkWords f0 = fetch_links(U, (t * v3 + s) * 4 + 3),
+                        f1 = fetch_links(U, ((t + 1 < t1 ? t + 1 : t) * v3 + s) * 4 + 3),
+                        f2 = fetch_links(U, ((t + 2 < t1 ? t + 2 : t) * v3 + s) * 4 + 3);
+        stage_links(f0, lds);
+        P = row_mul(P, lds);
+        if (t + 1 < t1) {
+            stage_links(f1, lds);
+            P = row_mul(P, lds);
         }
-    return c;
-}
-
-// Per spatial site s: (1/3) tr prod_{t = 0..Lt-1} U_t(s, t); block partials
-// (Re, Im) in partial[2 * b + {0, 1}].
-__global__ void __launch_bounds__(kB) k_poly_partial(const double *U, int v3, int Lt, double *partial)
-{
-    __shared__ double sh[kB];
-    const int s = blockIdx.x * kB + threadIdx.x;
-    double re = 0.0, im = 0.0;
-    if (s < v3) {
-        C3 P = load3(U + ((size_t)s * 4 + 3) * 18);
-        for (int t = 1; t < Lt; t++) P = mul3(P, load3(U + (((size_t)t * v3 + s) * 4 + 3) * 18));
-        re = (P.e[0].x + P.e[4].x + P.e[8].x) / 3.0;
-        im = (P.e[0].y + P.e[4].y + P.e[8].y) / 3.0;
+        if (t + 2 < t1) {
+            stage_links(f2, lds);
+            P = row_mul(P, lds);
+        }
     }
-    const double tr = block_sum(re, sh);
+    __syncthreads();  // (all lanes are done with the staged links)
+#pragma unroll
+    for (int k = 0; k < 3; k++) lds[lane * 3 + k] = dbl2_t{P.e[k].x, P.e[k].y};
     __syncthreads();
-    const double ti = block_sum(im, sh);
-    if (threadIdx.x == 0) {
-        partial[2 * blockIdx.x] = tr;
-        partial[2 * blockIdx.x + 1] = ti;
+    if (w != 0) return;
+    for (int q = 1; q < kPolySeg; q++) P = row_mul(P, sh[q]);
+    const bool live = lane < 3 * kRowLinks && s0 < v3;
+    double re = row == 0 ? P.e[0].x : (row == 1 ? P.e[1].x : P.e[2].x);
+    double im = row == 0 ? P.e[0].y : (row == 1 ? P.e[1].y : P.e[2].y);
+    re = live ? re / 3.0 : 0.0;
+    im = live ? im / 3.0 : 0.0;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        re += __shfl_xor(re, off, 64);
+        im += __shfl_xor(im, off, 64);
+    }
+    if (lane == 0) {
+        partial[2 * blockIdx.x] = re;
+        partial[2 * blockIdx.x + 1] = im;
     }
 }
 
-__global__ void k_poly_final(const double *partial, int nb, int v3, double *out)
+// out = sum over the nb partials / v3, each lane of one wave every 64th, then
+// a fixed tree
+__global__ void __launch_bounds__(64) k_poly_final(const double *partial, int nb, int v3, double *out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double re = 0.0, im = 0.0;
-    for (int b = 0; b < nb; b++) {
+    for (int b = threadIdx.x; b < nb; b += 64) {
         re += partial[2 * b];
         im += partial[2 * b + 1];
     }
-    out[0] = re / v3;
-    out[1] = im / v3;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        re += __shfl_xor(re, off, 64);
+        im += __shfl_xor(im, off, 64);
+    }
+    if (threadIdx.x == 0) {
+        out[0] = re / v3;
+        out[1] = im / v3;
+    }
 }
 
 wd_status check_src(const wd_ctx *c, const int32_t src[4])
@@ -224,11 +235,11 @@ extern "C" wd_status wd_polyakov(wd_ctx *c, const double *U, double *out)
     if (!c || !U || !out) return set_error(WD_ERR_ARG, "NULL argument");
     WD_HIP(hipSetDevice(c->device));
     const int v3 = c->dims[0] * c->dims[1] * c->dims[2], Lt = c->dims[3];
-    const int nb = (int)nblk(v3);
+    const int nb = (v3 + kRowLinks - 1) / kRowLinks;
     void *vp;
     WD_TRY(ws_get(c, "ms_poly", sizeof(double) * (2 * nb + 2), &vp));
     double *partial = (double *)vp, *res = partial + 2 * nb;
-    hipLaunchKernelGGL(k_poly_partial, dim3(nb), dim3(kB), 0, c->stream, U, v3, Lt, partial);
+    hipLaunchKernelGGL(k_poly_partial, dim3(nb), dim3(64 * kPolySeg), 0, c->stream, U, v3, Lt, partial);
     hipLaunchKernelGGL(k_poly_final, dim3(1), dim3(64), 0, c->stream, partial, nb, v3, res);
     HIPCHK(hipGetLastError());
     return read_back(c, out, res, 2);
