@@ -97,7 +97,8 @@ struct BatchSolver {
     double *coef1 = nullptr, *coef2 = nullptr, *partial = nullptr, *partial2 = nullptr;
     double *rr_s = nullptr;  // recursive |r|^2 saved at a reliable update
     double *ahist = nullptr; // alpha of the iterations since the last flush, [kRing][cap]
-    double *hbuf = nullptr;  // pinned, cap doubles
+    double *hbuf = nullptr;  // pinned, cap doubles and cap ints
+    int *ibuf = nullptr;     // the ints of it
     int *act = nullptr, *act64 = nullptr, *lst = nullptr;  // device id lists
     std::vector<int> state, iters, iters64, rus, status, last_ru, stall, active, active64;
     std::vector<double> bbh, maxrr, best, tres, kap;
@@ -198,7 +199,8 @@ struct BatchSolver {
         if (!mixed) lane_s = lane_d;
         if (hbuf) (void)hipHostFree(hbuf);
         hbuf = nullptr;
-        WD_HIP(hipHostMalloc((void **)&hbuf, sizeof(double) * cap, hipHostMallocDefault));
+        WD_HIP(hipHostMalloc((void **)&hbuf, (sizeof(double) + sizeof(int)) * cap, hipHostMallocDefault));
+        ibuf = (int *)(hbuf + cap);
         return WD_OK;
     }
 
@@ -629,6 +631,48 @@ struct BatchSolver {
         return WD_OK;
     }
 
+    // Whether the steps run in one launch per call (cg_small.hip): an FP64
+    // solve of a lattice that fits one work-group.  Its results are those of
+    // the launches it replaces, bit for bit; graphs = 0 and the per-launch
+    // timing ask for the launches.
+    bool small() const { return !mixed && p.graphs && !c->timing && cg_small_ok(c->g, nsub); }
+
+    // Steps of k iterations of every running RHS in one launch: each stops
+    // where it needs the host (see SmallArgs) or after max_steps.
+    wd_status small_steps(int k, int max_steps)
+    {
+        const hipStream_t s = c->stream;
+        SmallArgs a;
+        a.g = c->g;
+        a.links = c->links64;
+        a.p = lane_s.P;
+        a.r = lane_s.R;
+        a.x = lane_s.X;
+        a.coef = p.eo ? coef2 : coef1;
+        a.bb = bb;
+        a.rr = rr;
+        a.alpha = alpha;
+        a.beta = beta;
+        a.it_out = act64;  // (an FP64 solve has no second lane: its id list is free)
+        a.tol2 = p.tol * p.tol;
+        a.k = k;
+        a.maxiter = p.maxiter;
+        a.max_steps = max_steps;
+        for (size_t b = 0; b < active.size(); b += kSmallBatch) {
+            const int n = (int)std::min(active.size() - b, (size_t)kSmallBatch);
+            for (int q = 0; q < n; q++) {
+                a.rid[q] = active[b + q];
+                a.it[q] = iters[active[b + q]];
+            }
+            HIPCHK(cg_small_launch(a, n, c->lk64, p.eo != 0, s));
+        }
+        HIPCHK(hipMemcpyAsync(ibuf, act64, sizeof(int) * cap, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        for (int j : active) iters[j] = ibuf[j];
+        return checks();
+    }
+
     // k iterations of every running RHS, then the residual checks.
     wd_status step(int k)
     {
@@ -647,6 +691,13 @@ struct BatchSolver {
         }
         HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        return checks();
+    }
+
+    // The residual checks after a step, |r|^2 of every slot in hbuf.
+    wd_status checks()
+    {
+        const hipStream_t s = c->stream;
         const double tol2 = p.tol * p.tol, d2 = p.delta * p.delta;
         std::vector<double> rrh(cap, 0.0), r2s(cap, 0.0);
         std::vector<int> ru[2], keep[2];
@@ -825,6 +876,8 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     WD_TRY(bs.init(c, nrhs, p, "cg_"));
     WD_TRY(bs.add(phi, nrhs, kappa, nullptr, p.initial_guess ? x : nullptr));
     int it = 0;
+    // (every call of small_steps advances each running RHS to maxiter at most)
+    while (bs.running() && p.maxiter > 0 && bs.small()) WD_TRY(bs.small_steps(p.poll, p.maxiter));
     while (bs.running() && it < p.maxiter) {
         const int k = std::min(p.poll, p.maxiter - it);
         WD_TRY(bs.step(k));
@@ -908,6 +961,7 @@ extern "C" wd_status wd_session_step(wd_session *s, int k_iters)
     WD_HIP(hipSetDevice(c->device));
     TunedScope tscope{c, c->use_tuned};
     c->use_tuned = s->bs.p.tuned != 0;
+    if (s->bs.small() && s->bs.running()) return s->bs.small_steps(k_iters, 1);
     return s->bs.step(k_iters);
 }
 

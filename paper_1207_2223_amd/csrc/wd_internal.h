@@ -153,6 +153,25 @@ hipError_t op_launch_f32(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, i
 hipError_t op_launch_f16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
 hipError_t op_launch_i16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
 
+// CG steps of small lattices in one launch (cg_small.hip): one work-group per
+// listed right-hand side runs steps of k iterations until its |r|^2 is not
+// above tol2 * bb, not finite, or it reaches maxiter, at most max_steps.
+constexpr int kSmallSites = 256;  // sites of a vector
+constexpr int kSmallBatch = 32;   // right-hand sides of a launch
+struct SmallArgs {
+    Geom g;
+    const char *links = nullptr;
+    Field p, r, x;  // FP64
+    const double *coef = nullptr, *bb = nullptr;  // [rid]
+    double *rr = nullptr, *alpha = nullptr, *beta = nullptr;
+    int *it_out = nullptr;  // [rid] iterations done
+    double tol2 = 0.0;
+    int k = 1, maxiter = 0, max_steps = 1;
+    int rid[kSmallBatch] = {}, it[kSmallBatch] = {};  // and the iterations each has behind it
+};
+bool cg_small_ok(const Geom &g, int nsub);
+hipError_t cg_small_launch(const SmallArgs &a, int nrhs, int lk, bool eo, hipStream_t s);
+
 // BLAS-1 / reductions (blas.hip).  All take an active-RHS list.
 enum { FIN_STORE = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_RR = 3 };
 hipError_t blas_norm(const Field &a, int Vh, const int *active, int nact, double *partial,
