@@ -100,14 +100,55 @@ wd_status decode_prec(const wd_ctx *c, int prec, int *sp, int *lk, int *xp)
     return WD_OK;
 }
 
-TuneCfg default_cfg(int sp)
+TuneCfg default_cfg()
 {
     TuneCfg t;
     t.block = 128;
     t.nr = 1;
     t.rl = 1;
     t.remap = 1;
-    (void)sp;
+    return t;
+}
+
+// The launch shape of a sweep that has no tuned one (every shape gives the
+// same bits).  Lines drawn from the tuner's timings of all shapes; figures are
+// us a sweep, FP16 spinors unless said otherwise.
+static TuneCfg untuned_cfg(const wd_ctx *c, const Sweep &sw)
+{
+    TuneCfg t = default_cfg();
+    const long long work = c->Vh * sw.nact;
+    // one wavefront a work-group: 16^3 x 32 with one RHS 8.4 -> 7.8 (plain), 10.1
+    // -> 9.2 (CG update); with 8 RHS 27.5 -> 24.7; FP64 8^3 x 16 6.7 -> 6.0
+    t.block = 64;
+    // links of one RHS that exceed the last-level cache have no reuse: 32^3 x 64
+    // 102 -> 89 us, FP64 322 -> 306 (the same line as op_sweep's)
+    if (sw.nact == 1 && (double)c->Vh * 8.0 * (double)link_bytes(sw.lk) > 180e6 && lnt_ok(sw.sp, sw.lk, t)) t.lnt = 1;
+    if (sw.sp != SP_F64) {
+        // two RHS a lane share the link and its rebuilt row; with the
+        // epilogue's operands that pays once the chip is full (16^3 x 32, 8
+        // RHS: xpay 32.0 -> 29.5, CG update 35.3 -> 32.0; 24^3 x 48 151 -> 144,
+        // 169 -> 160), below it the lanes are missed (12^3 x 24, 5 RHS: 9.3 ->
+        // 10.0), and plain sweeps gain nothing (24^3 x 24, 6 RHS: 46.9 -> 49.2)
+        if (sw.epi != EPI_PLAIN && sw.nact >= 4 && work >= 250000 && dslash_shape_supported(sw.sp, sw.lk, 2, 1)) t.nr = 2;
+        return t;
+    }
+    if (sw.nact < 2 || work < 100000) return t;
+    if (slab_order_ok(c->g, 64, 6)) {
+        // a t slab per XCD, few sites in flight: 16^3 x 32, 8 RHS: plain 85.7
+        // -> 65.6 at 2 work-groups of 128 a CU, xpay 109 -> 90 with two lanes a
+        // site; 16^4, 12 RHS: 62.7 -> 51.1, 83.2 -> 71.3
+        const bool plain = sw.epi == EPI_PLAIN, b128 = slab_order_ok(c->g, plain ? 128 : 64, 6);
+        t.remap = 6;
+        t.rl = plain ? 1 : 2;
+        t.block = b128 ? 128 : 64;
+        t.occ = !plain ? 0 : (b128 ? 2 : 4);
+    } else if (slab_order_ok(c->g, 32, 2)) {
+        // a z slab per XCD: 24^3 x 48, 8 RHS: 495 -> 440, 587 -> 504
+        t.remap = 2;
+        t.rl = 2;
+    } else {
+        t.nr = 2;  // 12^3 x 24, 5 RHS: 18.1 -> 16.2, 23.6 -> 21.2
+    }
     return t;
 }
 
@@ -165,7 +206,7 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
 {
     if (sw.nact <= 0) return WD_OK;
     if (!cfg && c->use_tuned) cfg = tuned_cfg(c, sw);
-    TuneCfg t = cfg ? *cfg : default_cfg(sw.sp);
+    TuneCfg t = cfg ? *cfg : untuned_cfg(c, sw);
     if (!dslash_shape_supported(sw.sp, sw.lk, t.nr, t.rl) || t.block < 64 || t.block > 256 || (t.block & 63))
         return set_error(WD_ERR_ARG, "unsupported launch shape block %d nr %d rl %d", t.block, t.nr, t.rl);
     if (t.lnt != 0 && (t.lnt != 1 || !lnt_ok(sw.sp, sw.lk, t)))
@@ -604,7 +645,7 @@ wd_status wd_dslash_shaped(wd_ctx *c, double *out, const double *in, int nrhs, i
     if (nrhs < 1 || nrhs > 64) return set_error(WD_ERR_ARG, "nrhs %d out of range 1..64", nrhs);
     int sp, lk, xp;
     WD_TRY(decode_prec(c, prec, &sp, &lk, &xp));
-    TuneCfg t = default_cfg(sp);
+    TuneCfg t = default_cfg();
     if (shape) {
         t.block = shape[0];
         t.nr = shape[1];

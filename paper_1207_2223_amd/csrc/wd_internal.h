@@ -312,7 +312,7 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg);
 wd_status upload_doubles(wd_ctx *c, const std::string &name, const double *v, int n, double **dev);
 wd_status upload_ints(wd_ctx *c, const std::string &name, const int *v, int n, int **dev);
 Field sub_view(const Field &f, int s);
-TuneCfg default_cfg(int sp);
+TuneCfg default_cfg();
 // Whether the z-slab tile order (remap 2) applies to tiles of spb sites.
 // Tile orders: 0 plain, 1 XCD round-robin, 2-4 z-slab per XCD in 1/2/4
 // y-stripes, 5-6 t-slab per XCD walked t-fastest, 7 z-slab per XCD with the

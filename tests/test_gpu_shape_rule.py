@@ -1,0 +1,36 @@
+"""The launch shapes chosen for sweeps that are not tuned: a batch of the size
+at which each branch of the rule is taken gives each right-hand side the bits
+of its single solve (which takes the one-RHS shape).  Twenty iterations are
+enough for every sweep of the iteration and an FP64 reliable update."""
+import numpy as np
+import pytest
+
+import lattice_inputs as li
+from gpu_util import dev, empty_like_dev, host, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,nrhs", [((16, 16, 16, 8), 7),    # t slabs, 128-site tiles
+                                       ((8, 16, 18, 16), 6),    # t slabs, 64-site tiles
+                                       ((16, 12, 16, 18), 4),   # z slabs, 32-site tiles
+                                       ((12, 12, 12, 12), 26),  # two RHS a lane
+                                       ((16, 16, 16, 16), 8)])  # FP16 xpay and CG update with two RHS a lane
+@pytest.mark.parametrize("prec", ["f64", "f16", "f32r8"])
+def test_batch_equals_single_solves(prec, dims, nrhs):
+    from paper_1207_2223_amd import wd
+    code = {"f64": wd.WD_F64, "f16": wd.WD_F16, "f32r8": wd.WD_F32 | wd.WD_LINKS_R8}[prec]
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.4, seed=61)), recon=12)
+    B = li.gaussian_spinor(li.volume(dims) // 2, seed=62, nrhs=nrhs)
+    kap = np.linspace(0.12, 0.14, nrhs)
+    p = wd.solver_params(prec=code, maxiter=20, tol=1e-14, delta=0.3)
+    x = empty_like_dev(B)
+    lat.cg_solve(x, dev(B), kap, p)
+    X = host(x).view(np.uint64)
+    for j in (0, nrhs - 1):
+        y = empty_like_dev(B[j:j + 1])
+        lat.cg_solve(y, dev(B[j:j + 1]), kap[j:j + 1], p)
+        note(f"shape rule {prec} {dims} rhs {j}")
+        assert np.array_equal(host(y).view(np.uint64)[0], X[j])
+    lat.close()
