@@ -10,7 +10,47 @@ namespace wd {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kFinBlock = kFinLanes;
+
+// fin_wave_sum's value (the order of every CG scalar's sum) by a work-group of
+// kBlock threads: thread t sums the virtual lanes t + kBlock q, pairs them as
+// the halving tree does, ((q0 + q2) + (q1 + q3)), and the rest of the tree
+// pairs threads: two levels over LDS, six within the first wave.  The result
+// is in every thread; sh: kBlock doubles, free again after the call's last
+// barrier.  (One thread a virtual lane, a barrier a level: 4.4 us for the 4096
+// partials of 16^3 x 32 with one RHS, 3.2 now.)
+__device__ __forceinline__ double fin_block_sum(const double *pp, int nw, double *sh)
+{
+    static_assert(kFinLanes == 4 * kBlock, "four virtual lanes a thread");
+    const int t = (int)threadIdx.x;
+    double q[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int w0 = 0; w0 < nw; w0 += 4 * kFinLanes) {
+        double x[4][4];
+#pragma unroll
+        for (int m = 0; m < 4; m++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int w = w0 + t + kBlock * i + m * kFinLanes;
+                x[i][m] = w < nw ? pp[w] : 0.0;
+            }
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int m = 0; m < 4; m++) q[i] += x[i][m];
+    }
+    sh[t] = (q[0] + q[2]) + (q[1] + q[3]);
+    __syncthreads();
+    if (t < 64) {
+        double v = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double o = __shfl_down(v, off, 64);
+            if (t < off) v += o;
+        }
+        if (t == 0) sh[0] = v;
+    }
+    __syncthreads();
+    return sh[0];
+}
 
 __device__ __forceinline__ double sum16(double v)
 {
@@ -74,38 +114,67 @@ struct Ring {
     long long rs;
 };
 
+// beta of an iteration, finalized by every work-group of the p update for
+// itself: beta = (sum of the nw partials) / rr_in, written with the sum to
+// beta and rr_out by the first work-group of a RHS (rr_in and rr_out differ,
+// so that no other reads what it writes).  partial == nullptr: beta is read.
+struct BetaArg {
+    const double *partial;
+    int pstride, nw;
+    const double *rr_in;
+    double *rr_out, *beta;
+};
+
 // pd = r + beta p[m-1]; with FLUSH first x += alpha_j p[j] for j = 0..m-1,
 // in that order (the order and roundings of advancing x once per iteration).
+// Bound by memory; p and r are loaded before the sum for beta is waited for.
+// The sum saves a launch an iteration (finalize and its gap, 4-6 us) and costs
+// each work-group nw doubles from the L2: 8^3 x 16 3.0 -> 3.8 us, 16^3 x 32 5.4
+// -> 6.4.
 template <int SP, int XP, bool FLUSH>
-__global__ void __launch_bounds__(kBlock) k_p_update_ring(Ring p, int m, FArg pd, FArg r, const double *beta,
+__global__ void __launch_bounds__(kBlock) k_p_update_ring(Ring p, int m, FArg pd, FArg r, BetaArg bt,
                                                            FArg x, const double *ahist, int ahs, int Vh,
                                                            const int *active)
 {
     typedef typename SpinorIO<SP>::real real;
     typedef typename SpinorIO<XP>::real xreal;
+    __shared__ double sh[kBlock];
     const int rid = active[blockIdx.y];
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= Vh) return;
-    real pv[24];
+    const bool live = i < Vh;
+    const int is = live ? i : Vh - 1;
+    real pv[24], rv[24];
     if constexpr (FLUSH) {
-        xreal xv[24];
-        SpinorIO<XP>::load(x.base + rid * x.rs, x.cs, i, xv);
+        if (live) {
+            xreal xv[24];
+            SpinorIO<XP>::load(x.base + rid * x.rs, x.cs, i, xv);
 #pragma unroll
-        for (int j = 0; j < kMaxRing; j++) {
-            if (j < m) {
-                const real al = (real)ahist[(size_t)j * ahs + rid];
-                SpinorIO<SP>::load(p.base[j] + rid * p.rs, pd.cs, i, pv);
+            for (int j = 0; j < kMaxRing; j++) {
+                if (j < m) {
+                    const real al = (real)ahist[(size_t)j * ahs + rid];
+                    SpinorIO<SP>::load(p.base[j] + rid * p.rs, pd.cs, i, pv);
 #pragma unroll
-                for (int k = 0; k < 24; k++) xv[k] = fmaT((xreal)al, (xreal)pv[k], xv[k]);
+                    for (int k = 0; k < 24; k++) xv[k] = fmaT((xreal)al, (xreal)pv[k], xv[k]);
+                }
             }
+            SpinorIO<XP>::store(x.base + rid * x.rs, x.cs, i, xv);
         }
-        SpinorIO<XP>::store(x.base + rid * x.rs, x.cs, i, xv);
     } else {
-        SpinorIO<SP>::load(p.base[m - 1] + rid * p.rs, pd.cs, i, pv);
+        SpinorIO<SP>::load(p.base[m - 1] + rid * p.rs, pd.cs, is, pv);
     }
-    real rv[24];
-    SpinorIO<SP>::load(r.base + rid * r.rs, r.cs, i, rv);
-    const real b = (real)beta[rid];
+    SpinorIO<SP>::load(r.base + rid * r.rs, r.cs, is, rv);
+    real b;
+    if (bt.partial) {
+        const double s = fin_block_sum(bt.partial + (size_t)rid * bt.pstride, bt.nw, sh), bd = s / bt.rr_in[rid];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            bt.rr_out[rid] = s;
+            bt.beta[rid] = bd;
+        }
+        b = (real)bd;
+    } else {
+        b = (real)bt.beta[rid];
+    }
+    if (!live) return;
 #pragma unroll
     for (int k = 0; k < 24; k++) pv[k] = fmaT(b, pv[k], rv[k]);
     SpinorIO<SP>::store(pd.base + rid * pd.rs, pd.cs, i, pv);
@@ -310,21 +379,14 @@ __global__ void __launch_bounds__(kBlock) k_xpay_ratio(FArg p, FArg r, const dou
 
 // One work-group per active RHS: fixed-order sum of its partials, then the
 // CG scalar update selected by mode.
-__global__ void __launch_bounds__(kFinBlock) k_finalize(const double *partial, int pstride, int nw,
-                                                         const int *active, int mode, double *rr,
-                                                         double *alpha, double *beta, double *out)
+__global__ void __launch_bounds__(kBlock) k_finalize(const double *partial, int pstride, int nw,
+                                                      const int *active, int mode, double *rr,
+                                                      double *alpha, double *beta, double *out)
 {
-    __shared__ double sh[kFinBlock];
+    __shared__ double sh[kBlock];
     const int rid = active[blockIdx.x];
-    const double v = fin_lane_sum(partial + (size_t)rid * pstride, nw, threadIdx.x);
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = kFinBlock / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-        __syncthreads();
-    }
+    const double s = fin_block_sum(partial + (size_t)rid * pstride, nw, sh);
     if (threadIdx.x == 0) {
-        const double s = sh[0];
         if (mode == FIN_STORE) {
             out[rid] = s;
         } else if (mode == FIN_ALPHA) {
@@ -373,8 +435,8 @@ hipError_t blas_p_update(const Field &p, const Field &r, const double *beta, int
     return hipGetLastError();
 }
 
-hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Field &r, const double *beta,
-                              bool flush, const Field &x, const double *ahist, int ahs, int Vh,
+hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Field &r, const BetaFold &bf,
+                              double *beta, bool flush, const Field &x, const double *ahist, int ahs, int Vh,
                               const int *active, int nact, hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
@@ -382,14 +444,15 @@ hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Fi
     Ring R{};
     for (int j = 0; j < m; j++) R.base[j] = p[j].base;
     R.rs = p[0].rs;
+    const BetaArg bt{bf.partial, bf.pstride, bf.nw, bf.rr_in, bf.rr_out, beta};
     const dim3 grid = grid_of(Vh, 1, nact);
 #define F(SP_, XP_)                                                                                       \
     if (flush)                                                                                            \
         hipLaunchKernelGGL((k_p_update_ring<SP_, XP_, true>), grid, dim3(kBlock), 0, s, R, m, fa(pdst), fa(r), \
-                           beta, fa(x), ahist, ahs, Vh, active);                                          \
+                           bt, fa(x), ahist, ahs, Vh, active);                                            \
     else                                                                                                  \
         hipLaunchKernelGGL((k_p_update_ring<SP_, XP_, false>), grid, dim3(kBlock), 0, s, R, m, fa(pdst),     \
-                           fa(r), beta, fa(x), ahist, ahs, Vh, active);
+                           fa(r), bt, fa(x), ahist, ahs, Vh, active);
     if (pdst.sp == SP_F64 && (!flush || x.sp == SP_F64)) {
         F(SP_F64, SP_F64)
     } else if (pdst.sp != SP_F64 && (!flush || x.sp == SP_F32)) {
@@ -524,7 +587,7 @@ hipError_t blas_finalize(const double *partial, int pstride, int nw, const int *
                          hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize, dim3(nact), dim3(kFinBlock), 0, s, partial, pstride, nw, active, mode, rr, alpha, beta, out);
+    hipLaunchKernelGGL(k_finalize, dim3(nact), dim3(kBlock), 0, s, partial, pstride, nw, active, mode, rr, alpha, beta, out);
     return hipGetLastError();
 }
 

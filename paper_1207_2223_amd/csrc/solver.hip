@@ -11,8 +11,8 @@
 //   alpha = rr / pAp                                  work-groups finalize alpha)
 //   Ap   = t2 - k^2 D_eo^dag t_o;  r -= alpha Ap;  rr' = |r|^2
 //                                                    (sweep 4, fused update)
-//   beta = rr' / rr                                  (finalize, on device)
-//   p'   = r + beta p
+//   beta = rr' / rr                                  (in the p update, or its
+//   p'   = r + beta p                                  own launch for big batches)
 // alpha and beta never leave the device; the host reads the residual norms
 // after every step of k iterations.  The solution is not touched by the
 // iteration itself: each iteration's p goes to its own slot of a ring of
@@ -79,7 +79,7 @@ struct BatchSolver {
     // restart p = r when the true residual exceeds the recursive one by more
     // than this factor (in |r|^2): the recursion has lost its accuracy
     static constexpr double kDriftRestart = 4.0;
-    static constexpr int kScalars = 9;  // per-slot device scalars (bb .. rr_s)
+    static constexpr int kScalars = 10;  // per-slot device scalars (bb .. rr_b)
     // directions kept between solution flushes (even-odd lanes; a mixed
     // solve's FP64 lane, used by escalated RHS only, flushes every iteration)
     static constexpr int kRing = kMaxRing;
@@ -96,6 +96,7 @@ struct BatchSolver {
     double *bb = nullptr, *rr = nullptr, *alpha = nullptr, *beta = nullptr, *dre = nullptr, *dim = nullptr;
     double *coef1 = nullptr, *coef2 = nullptr, *partial = nullptr, *partial2 = nullptr;
     double *rr_s = nullptr;  // recursive |r|^2 saved at a reliable update
+    double *rr_b = nullptr;  // |r|^2 after every other iteration of a step (see iterate)
     double *ahist = nullptr; // alpha of the iterations since the last flush, [kRing][cap]
     double *hbuf = nullptr;  // pinned, cap doubles and cap ints
     int *ibuf = nullptr;     // the ints of it
@@ -162,6 +163,7 @@ struct BatchSolver {
         coef1 = dim + cap;
         coef2 = coef1 + cap;
         rr_s = coef2 + cap;
+        rr_b = rr_s + cap;
         WD_TRY(ws_get(c, nm("partial"), sizeof(double) * pstride * cap * 2, &vp));
         partial = (double *)vp;
         partial2 = partial + (size_t)pstride * cap;
@@ -372,13 +374,28 @@ struct BatchSolver {
     // Ring slots of a lane (1 for the full-lattice iteration).
     static int ring_of(const Lane &L) { return (int)L.Pr.size(); }
 
+    // Where the p update sums the partials of |r|^2 itself instead of a finalize
+    // launch: up to so many of them, and so many bytes of them read by all its
+    // work-groups.  HMC 8^3 x 16 33.4 -> 30.7 ms, session 12^3 x 24 with 5 RHS
+    // 10.25 -> 10.0, force 16^3 x 32 11.05 -> 10.8; 8 RHS at 16^3 x 32 would
+    // read 67 MB, as long as the launch takes.
+    static constexpr int kFoldPartials = 4096;
+    static constexpr long long kFoldReads = 8LL << 20;
+
     // One CG iteration of the listed RHS of a lane (see the file header):
     // iteration j of the lane's ring cycle; flush: the p update advances the
     // solution by the directions of iterations 0..j and puts the new
-    // direction back in slot 0.
-    wd_status iterate(const Lane &L, const int *ids, int n, int j, bool flush)
+    // direction back in slot 0.  kk, last: its number in the step, and whether
+    // it is the step's last.  Where the p update finalizes beta, |r|^2 goes to
+    // and fro between rr and rr_b (its work-groups read the old value while
+    // one writes the new) and a step ends with it in rr.
+    wd_status iterate(const Lane &L, const int *ids, int n, int j, bool flush, int kk, bool last)
     {
         const hipStream_t s = c->stream;
+        double *const rr_in = kk & 1 ? rr_b : rr, *const rr_out = kk & 1 ? rr : rr_b;
+        const long long reads = (long long)n * ((Vh + 255) / 256) * nw1 * 8;
+        const bool pp = p.eo && fold && nw1 <= kFoldPartials && reads <= kFoldReads;  // (the same for every kk of a step)
+        double *const rr = pp ? rr_in : this->rr;
         if (p.eo) {
             const Field &Pj = L.Pr[j];
             Sweep sw;
@@ -406,12 +423,21 @@ struct BatchSolver {
             sw.P = 0; sw.epi = EPI_CGUPD; sw.in = L.TO; sw.x = L.T2; sw.r = L.R;
             sw.alpha = alpha; sw.partial = partial;
             WD_TRY(run_sweep(c, sw, nullptr));
-            HIPCHK(blas_finalize(partial, pstride, nw1, ids, n, FIN_BETA, rr, alpha, beta, nullptr, s));
+            BetaFold bf;
+            if (pp && !(last && rr_out != this->rr)) {
+                bf.partial = partial;
+                bf.pstride = pstride;
+                bf.nw = nw1;
+                bf.rr_in = rr;
+                bf.rr_out = rr_out;
+            } else {
+                HIPCHK(blas_finalize(partial, pstride, nw1, ids, n, FIN_BETA, rr, alpha, beta, nullptr, s));
+            }
             if (flush)
-                HIPCHK(blas_p_update_ring(L.Pr.data(), j + 1, L.Pr[0], L.R, beta, true, L.X, ahist, cap, Vh, ids,
+                HIPCHK(blas_p_update_ring(L.Pr.data(), j + 1, L.Pr[0], L.R, bf, beta, true, L.X, ahist, cap, Vh, ids,
                                           n, s));
             else
-                HIPCHK(blas_p_update_ring(&L.Pr[j], 1, L.Pr[j + 1], L.R, beta, false, L.X, ahist, cap, Vh, ids,
+                HIPCHK(blas_p_update_ring(&L.Pr[j], 1, L.Pr[j + 1], L.R, bf, beta, false, L.X, ahist, cap, Vh, ids,
                                           n, s));
         } else {
             WD_TRY(apply_A(L.sp, L.lk, L.P, Ap64, ids, n, true));
@@ -431,11 +457,11 @@ struct BatchSolver {
         for (int kk = 0; kk < k; kk++) {
             if (nact) {
                 const int R = ring_of(lane_s), j = kk % R;
-                WD_TRY(iterate(lane_s, act, nact, j, j == R - 1 || kk == k - 1));
+                WD_TRY(iterate(lane_s, act, nact, j, j == R - 1 || kk == k - 1, kk, kk == k - 1));
             }
             if (nact64) {
                 const int R = ring_of(lane_d), j = kk % R;
-                WD_TRY(iterate(lane_d, act64, nact64, j, j == R - 1 || kk == k - 1));
+                WD_TRY(iterate(lane_d, act64, nact64, j, j == R - 1 || kk == k - 1, kk, kk == k - 1));
             }
         }
         return WD_OK;

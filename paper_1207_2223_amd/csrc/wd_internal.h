@@ -183,9 +183,17 @@ hipError_t blas_p_update(const Field &p, const Field &r, const double *beta, int
 // last m iterations (slots of a ring, p[m-1] the current one); with flush,
 // first x += alpha_j p[j] for j = 0 .. m-1 in that order (alpha_j =
 // ahist[j*ahs + rid]), the same roundings as advancing x every iteration.
+// bf.partial: beta is finalized there, from |r|^2's nw partials and rr_in, the
+// new |r|^2 going to rr_out (not rr_in); null: beta is read.
 constexpr int kMaxRing = 8;
-hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Field &r, const double *beta,
-                              bool flush, const Field &x, const double *ahist, int ahs, int Vh,
+struct BetaFold {
+    const double *partial = nullptr;
+    int pstride = 0, nw = 0;
+    const double *rr_in = nullptr;
+    double *rr_out = nullptr;
+};
+hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Field &r, const BetaFold &bf,
+                              double *beta, bool flush, const Field &x, const double *ahist, int ahs, int Vh,
                               const int *active, int nact, hipStream_t s);
 hipError_t blas_cg_update(const Field &x, const Field &p, const Field &r, const Field &Ap,
                           const double *alpha, int Vh, const int *active, int nact,
