@@ -122,7 +122,7 @@ struct BetaArg {
     const double *partial;
     int pstride, nw;
     const double *rr_in;
-    double *rr_out, *beta;
+    double *rr_out, *beta, *hout;
 };
 
 // pd = r + beta p[m-1]; with FLUSH first x += alpha_j p[j] for j = 0..m-1,
@@ -169,6 +169,10 @@ __global__ void __launch_bounds__(kBlock) k_p_update_ring(Ring p, int m, FArg pd
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             bt.rr_out[rid] = s;
             bt.beta[rid] = bd;
+            if (bt.hout) {
+                bt.hout[rid] = s;
+                __threadfence_system();
+            }
         }
         b = (real)bd;
     } else {
@@ -213,81 +217,140 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(FArg x, FArg p, FArg r, FA
     if ((threadIdx.x & 15) == 0 && s < nsub * Vh) partial[(size_t)rid * pstride + (s >> 4)] = v;
 }
 
-template <int SPD, int SPS>
-__global__ void __launch_bounds__(kBlock) k_copy(FArg d, FArg src, int Vh, int nsub,
-                                                  const int *active)
+template <int SP>
+__global__ void __launch_bounds__(kBlock) k_copy(FArg d, FArg src, int Vh, int nsub, const int *active)
 {
     const int rid = active[blockIdx.y];
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= nsub * Vh) return;
     const int sub = s / Vh, i = s - sub * Vh;
     double v[24];
-    SpinorIO<SPS>::load(site_base(src, rid, sub), src.cs, i, v);
-    SpinorIO<SPD>::store(site_base(d, rid, sub), d.cs, i, v);
+    SpinorIO<SP>::load(site_base(src, rid, sub), src.cs, i, v);
+    SpinorIO<SP>::store(site_base(d, rid, sub), d.cs, i, v);
 }
 
-// xhi (FP64) += xs ; xs = 0
-template <int XP>
-__global__ void __launch_bounds__(kBlock) k_add_zero(FArg xhi, FArg xs, int Vh, int nsub,
-                                                      const int *active)
+// Store of 24 reals and what a load of them gives back.
+template <int SP, typename T>
+__device__ __forceinline__ void store_rt(char *f, int cs, int i, const T v[24], typename SpinorIO<SP>::real back[24])
 {
-    const int rid = active[blockIdx.y];
-    const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s >= nsub * Vh) return;
-    const int sub = s / Vh, i = s - sub * Vh;
-    double h[24], l[24];
-    SpinorIO<SP_F64>::load(site_base(xhi, rid, sub), xhi.cs, i, h);
-    SpinorIO<XP>::load(site_base(xs, rid, sub), xs.cs, i, l);
+    if constexpr (has_norm(SP)) {
+        uint32_t w[12];
+        const float n = SpinorIO<SP>::encode(v, w);
+        u32x4_t *p = reinterpret_cast<u32x4_t *>(f);
 #pragma unroll
-    for (int k = 0; k < 24; k++) {
-        h[k] += l[k];
-        l[k] = 0.0;
+        for (int k = 0; k < 3; k++) p[(size_t)k * cs + i] = u32x4_t{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
+        reinterpret_cast<float *>(f + (size_t)48 * cs)[i] = n;
+#pragma unroll
+        for (int k = 0; k < 12; k++) SpinorIO<SP>::decode(w[k], n, &back[2 * k], &back[2 * k + 1]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 24; k++) back[k] = (typename SpinorIO<SP>::real)v[k];
+        SpinorIO<SP>::store(f, cs, i, back);
     }
-    SpinorIO<SP_F64>::store(site_base(xhi, rid, sub), xhi.cs, i, h);
-    SpinorIO<XP>::store(site_base(xs, rid, sub), xs.cs, i, l);
 }
 
-// r = b - Ap, all FP64, with |r|^2 partials
-__global__ void __launch_bounds__(kBlock) k_resid(FArg r, FArg b, FArg Ap, int Vh, int nsub,
-                                                   const int *active, double *partial,
-                                                   int pstride)
+struct IdList {
+    int n;
+    int id[64];
+};
+__global__ void k_set_ids(int *dst, IdList l)
 {
+    if ((int)threadIdx.x < l.n) dst[threadIdx.x] = l.id[threadIdx.x];
+}
+
+struct CoefList {
+    int n;
+    int id[32];
+    double kappa[32];
+};
+__global__ void k_set_coefs(double *c1, double *c2, CoefList l)
+{
+    const int q = threadIdx.x;
+    if (q >= l.n) return;
+    const double k = l.kappa[q];
+    c1[l.id[q]] = -k;
+    c2[l.id[q]] = -k * k;
+}
+
+// (see blas_cg_init) One pass over the fields of a new right-hand side; as
+// separate norm, zero and copy launches it was seven.
+template <int SP, bool FRESH>
+__global__ void __launch_bounds__(kBlock) k_cg_init(FArg b, FArg x, FArg r, FArg rs, FArg xs, FArg p, int Vh, int nsub,
+                                                     const int *active, double *partial, int pstride)
+{
+    typedef typename SpinorIO<SP>::real real;
     const int rid = active[blockIdx.y];
     const int s = blockIdx.x * kBlock + threadIdx.x;
-    double v = 0.0;
+    double nrm = 0.0;
     if (s < nsub * Vh) {
         const int sub = s / Vh, i = s - sub * Vh;
-        double bv[24], av[24];
-        SpinorIO<SP_F64>::load(site_base(b, rid, sub), b.cs, i, bv);
-        SpinorIO<SP_F64>::load(site_base(Ap, rid, sub), Ap.cs, i, av);
+        double v[24];
+        SpinorIO<SP_F64>::load(site_base(FRESH ? b : r, rid, sub), b.cs, i, v);
+        if constexpr (FRESH) {
+            double z[24];
 #pragma unroll
-        for (int k = 0; k < 24; k++) {
-            bv[k] -= av[k];
-            v = fmaT(bv[k], bv[k], v);
+            for (int k = 0; k < 24; k++) {
+                nrm = fmaT(v[k], v[k], nrm);
+                z[k] = 0.0;
+            }
+            SpinorIO<SP_F64>::store(site_base(r, rid, sub), r.cs, i, v);
+            SpinorIO<SP_F64>::store(site_base(x, rid, sub), x.cs, i, z);
         }
-        SpinorIO<SP_F64>::store(site_base(r, rid, sub), r.cs, i, bv);
+        if constexpr (SP == SP_F64) {
+            SpinorIO<SP_F64>::store(site_base(p, rid, sub), p.cs, i, v);
+        } else {
+            float z[24];
+            real q[24], q2[24];
+#pragma unroll
+            for (int k = 0; k < 24; k++) z[k] = 0.f;
+            SpinorIO<SP_F32>::store(site_base(xs, rid, sub), xs.cs, i, z);
+            store_rt<SP>(site_base(rs, rid, sub), rs.cs, i, v, q);
+            store_rt<SP>(site_base(p, rid, sub), p.cs, i, q, q2);
+        }
     }
-    v = sum16(v);
-    if ((threadIdx.x & 15) == 0 && s < nsub * Vh) partial[(size_t)rid * pstride + (s >> 4)] = v;
+    if constexpr (FRESH) {
+        nrm = sum16(nrm);
+        if ((threadIdx.x & 15) == 0 && s < nsub * Vh) partial[(size_t)rid * pstride + (s >> 4)] = nrm;
+    }
 }
 
-template <int SP>
-__global__ void __launch_bounds__(kBlock) k_zero(FArg a, int Vh, int nsub, const int *active)
+// Reliable update, before the FP64 sweeps: p -= r; SLOPPY: xhi += xs, xs = 0;
+// the first work-group of a RHS keeps rr in rr_s.
+template <int SP, int XP, bool SLOPPY>
+__global__ void __launch_bounds__(kBlock) k_ru_begin(FArg p, FArg r, FArg xhi, FArg xs, const double *rr, double *rr_s,
+                                                      int Vh, int nsub, const int *active)
 {
+    typedef typename SpinorIO<SP>::real real;
     const int rid = active[blockIdx.y];
     const int s = blockIdx.x * kBlock + threadIdx.x;
+    if (s == 0) rr_s[rid] = rr[rid];
     if (s >= nsub * Vh) return;
     const int sub = s / Vh, i = s - sub * Vh;
-    double z[24];
+    real pv[24], rv[24];
+    SpinorIO<SP>::load(site_base(p, rid, sub), p.cs, i, pv);
+    SpinorIO<SP>::load(site_base(r, rid, sub), r.cs, i, rv);
 #pragma unroll
-    for (int k = 0; k < 24; k++) z[k] = 0.0;
-    SpinorIO<SP>::store(site_base(a, rid, sub), a.cs, i, z);
+    for (int k = 0; k < 24; k++) pv[k] = fmaT((real)-1, rv[k], pv[k]);
+    SpinorIO<SP>::store(site_base(p, rid, sub), p.cs, i, pv);
+    if constexpr (SLOPPY) {
+        double h[24], l[24];
+        SpinorIO<SP_F64>::load(site_base(xhi, rid, sub), xhi.cs, i, h);
+        SpinorIO<XP>::load(site_base(xs, rid, sub), xs.cs, i, l);
+#pragma unroll
+        for (int k = 0; k < 24; k++) {
+            h[k] += l[k];
+            l[k] = 0.0;
+        }
+        SpinorIO<SP_F64>::store(site_base(xhi, rid, sub), xhi.cs, i, h);
+        SpinorIO<XP>::store(site_base(xs, rid, sub), xs.cs, i, l);
+    }
 }
 
-// <a, b> = sum conj(a) b, real and imaginary partials
-template <int SP>
-__global__ void __launch_bounds__(kBlock) k_cdot(FArg a, FArg b, int Vh, int nsub, const int *active,
-                                                  double *pre, double *pim, int pstride)
+// After the sweeps: SLOPPY: r = r64 in the sloppy format; partials of <r, p> =
+// sum conj(r) p (r as stored).
+template <int SP, bool SLOPPY>
+__global__ void __launch_bounds__(kBlock) k_ru_mid(FArg r64, FArg r, FArg p, int Vh, int nsub, const int *active,
+                                                    double *pre, double *pim, int pstride)
 {
     typedef typename SpinorIO<SP>::real real;
     const int rid = active[blockIdx.y];
@@ -296,8 +359,14 @@ __global__ void __launch_bounds__(kBlock) k_cdot(FArg a, FArg b, int Vh, int nsu
     if (s < nsub * Vh) {
         const int sub = s / Vh, i = s - sub * Vh;
         real x[24], y[24];
-        SpinorIO<SP>::load(site_base(a, rid, sub), a.cs, i, x);
-        SpinorIO<SP>::load(site_base(b, rid, sub), b.cs, i, y);
+        if constexpr (SLOPPY) {
+            double v[24];
+            SpinorIO<SP_F64>::load(site_base(r64, rid, sub), r64.cs, i, v);
+            store_rt<SP>(site_base(r, rid, sub), r.cs, i, v, x);
+        } else {
+            SpinorIO<SP>::load(site_base(r, rid, sub), r.cs, i, x);
+        }
+        SpinorIO<SP>::load(site_base(p, rid, sub), p.cs, i, y);
 #pragma unroll
         for (int k = 0; k < 12; k++) {
             const double ar = x[2 * k], ai = x[2 * k + 1], br = y[2 * k], bi = y[2 * k + 1];
@@ -315,19 +384,41 @@ __global__ void __launch_bounds__(kBlock) k_cdot(FArg a, FArg b, int Vh, int nsu
     }
 }
 
-// p -= c r with c = <r, p> / rr (complex), per RHS
+// Three sums a RHS (blockIdx.x = 0: |r|^2, 1: Re <r, p>, 2: Im).
+__global__ void __launch_bounds__(kBlock) k_ru_sums(const double *prr, int nwr, const double *pre, const double *pim,
+                                                     int nw, int pstride, double *rr, double *hout, double *dre,
+                                                     double *dim, const int *active)
+{
+    __shared__ double sh[kBlock];
+    const int rid = active[blockIdx.y], which = blockIdx.x;
+    const double *pp = which == 0 ? prr : (which == 1 ? pre : pim);
+    const double s = fin_block_sum(pp + (size_t)rid * pstride, which == 0 ? nwr : nw, sh);
+    if (threadIdx.x != 0) return;
+    if (which == 0) {
+        rr[rid] = s;
+        hout[rid] = s;
+        __threadfence_system();
+    } else {
+        (which == 1 ? dre : dim)[rid] = s;
+    }
+}
+
+// p -= c r with c = <r, p> / rr (complex), kept in p's format, then p = r +
+// (rr / rr_s) p.
 template <int SP>
-__global__ void __launch_bounds__(kBlock) k_orth(FArg p, FArg r, const double *dre, const double *dim,
-                                                  const double *rr, int Vh, int nsub, const int *active)
+__global__ void __launch_bounds__(kBlock) k_ru_end(FArg p, FArg r, const double *dre, const double *dim,
+                                                    const double *rr, const double *rr_s, int Vh, int nsub,
+                                                    const int *active)
 {
     typedef typename SpinorIO<SP>::real real;
     const int rid = active[blockIdx.y];
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= nsub * Vh) return;
     const int sub = s / Vh, i = s - sub * Vh;
-    const double n = rr[rid];
+    const double n = rr[rid], d = rr_s[rid];
     const real cr = (real)(n > 0.0 ? dre[rid] / n : 0.0), ci = (real)(n > 0.0 ? dim[rid] / n : 0.0);
-    real pv[24], rv[24];
+    const real b = (real)(d > 0.0 ? n / d : 0.0);
+    real pv[24], rv[24], q[24];
     SpinorIO<SP>::load(site_base(p, rid, sub), p.cs, i, pv);
     SpinorIO<SP>::load(site_base(r, rid, sub), r.cs, i, rv);
 #pragma unroll
@@ -336,52 +427,25 @@ __global__ void __launch_bounds__(kBlock) k_orth(FArg p, FArg r, const double *d
         pv[2 * k] = fmaT(-cr, ar, fmaT(ci, ai, pv[2 * k]));
         pv[2 * k + 1] = fmaT(-cr, ai, fmaT(-ci, ar, pv[2 * k + 1]));
     }
-    SpinorIO<SP>::store(site_base(p, rid, sub), p.cs, i, pv);
-}
-
-// p += a r  (a a real constant)
-template <int SP>
-__global__ void __launch_bounds__(kBlock) k_axpy_const(FArg p, FArg r, double a, int Vh, int nsub,
-                                                        const int *active)
-{
-    typedef typename SpinorIO<SP>::real real;
-    const int rid = active[blockIdx.y];
-    const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s >= nsub * Vh) return;
-    const int sub = s / Vh, i = s - sub * Vh;
-    real pv[24], rv[24];
-    SpinorIO<SP>::load(site_base(p, rid, sub), p.cs, i, pv);
-    SpinorIO<SP>::load(site_base(r, rid, sub), r.cs, i, rv);
+    if constexpr (has_norm(SP)) {
+        uint32_t w[12];
+        const float m = SpinorIO<SP>::encode(pv, w);
 #pragma unroll
-    for (int k = 0; k < 24; k++) pv[k] = fmaT((real)a, rv[k], pv[k]);
-    SpinorIO<SP>::store(site_base(p, rid, sub), p.cs, i, pv);
-}
-
-// p = r + (num[rid] / den[rid]) p
-template <int SP>
-__global__ void __launch_bounds__(kBlock) k_xpay_ratio(FArg p, FArg r, const double *num, const double *den,
-                                                        int Vh, int nsub, const int *active)
-{
-    typedef typename SpinorIO<SP>::real real;
-    const int rid = active[blockIdx.y];
-    const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s >= nsub * Vh) return;
-    const int sub = s / Vh, i = s - sub * Vh;
-    const double d = den[rid];
-    const real b = (real)(d > 0.0 ? num[rid] / d : 0.0);
-    real pv[24], rv[24];
-    SpinorIO<SP>::load(site_base(p, rid, sub), p.cs, i, pv);
-    SpinorIO<SP>::load(site_base(r, rid, sub), r.cs, i, rv);
+        for (int k = 0; k < 12; k++) SpinorIO<SP>::decode(w[k], m, &q[2 * k], &q[2 * k + 1]);
+    } else {
 #pragma unroll
-    for (int k = 0; k < 24; k++) pv[k] = fmaT(b, pv[k], rv[k]);
-    SpinorIO<SP>::store(site_base(p, rid, sub), p.cs, i, pv);
+        for (int k = 0; k < 24; k++) q[k] = pv[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 24; k++) q[k] = fmaT(b, q[k], rv[k]);
+    SpinorIO<SP>::store(site_base(p, rid, sub), p.cs, i, q);
 }
 
 // One work-group per active RHS: fixed-order sum of its partials, then the
 // CG scalar update selected by mode.
 __global__ void __launch_bounds__(kBlock) k_finalize(const double *partial, int pstride, int nw,
                                                       const int *active, int mode, double *rr,
-                                                      double *alpha, double *beta, double *out)
+                                                      double *alpha, double *beta, double *out, double *hout)
 {
     __shared__ double sh[kBlock];
     const int rid = active[blockIdx.x];
@@ -397,6 +461,11 @@ __global__ void __launch_bounds__(kBlock) k_finalize(const double *partial, int 
             rr[rid] = s;
         } else {
             rr[rid] = s;
+            if (out) out[rid] = s;
+        }
+        if (hout) {
+            hout[rid] = s;
+            __threadfence_system();
         }
     }
 }
@@ -444,7 +513,7 @@ hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Fi
     Ring R{};
     for (int j = 0; j < m; j++) R.base[j] = p[j].base;
     R.rs = p[0].rs;
-    const BetaArg bt{bf.partial, bf.pstride, bf.nw, bf.rr_in, bf.rr_out, beta};
+    const BetaArg bt{bf.partial, bf.pstride, bf.nw, bf.rr_in, bf.rr_out, beta, bf.hout};
     const dim3 grid = grid_of(Vh, 1, nact);
 #define F(SP_, XP_)                                                                                       \
     if (flush)                                                                                            \
@@ -492,102 +561,119 @@ hipError_t blas_copy(const Field &dst, const Field &src, int Vh, const int *acti
                      hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
-    dim3 gr = grid_of(Vh, dst.nsub, nact);
-#define C2(D, S)                                                                                  \
-    if (dst.sp == D && src.sp == S) {                                                             \
-        hipLaunchKernelGGL((k_copy<D, S>), gr, dim3(kBlock), 0, s, fa(dst), fa(src), Vh, dst.nsub, active); \
-        return hipGetLastError();                                                                 \
+    if (dst.sp != src.sp) return hipErrorInvalidValue;
+#define F(SP) hipLaunchKernelGGL(k_copy<SP>, grid_of(Vh, dst.nsub, nact), dim3(kBlock), 0, s, fa(dst), fa(src), Vh, dst.nsub, active)
+    SP_SWITCH(dst.sp, F)
+#undef F
+    return hipGetLastError();
+}
+
+hipError_t blas_set_ids(int *dst, const int *ids, int n, hipStream_t s)
+{
+    for (int b = 0; b < n; b += 64) {
+        IdList l;
+        l.n = n - b < 64 ? n - b : 64;
+        for (int q = 0; q < 64; q++) l.id[q] = q < l.n ? ids[b + q] : 0;
+        hipLaunchKernelGGL(k_set_ids, dim3(1), dim3(64), 0, s, dst + b, l);
     }
-    C2(SP_F64, SP_F64) C2(SP_F64, SP_F32) C2(SP_F64, SP_F16)
-    C2(SP_F32, SP_F64) C2(SP_F32, SP_F32) C2(SP_F32, SP_F16)
-    C2(SP_F16, SP_F64) C2(SP_F16, SP_F32) C2(SP_F16, SP_F16)
-    C2(SP_F64, SP_I16) C2(SP_F32, SP_I16) C2(SP_I16, SP_F64) C2(SP_I16, SP_F32) C2(SP_I16, SP_I16)
-#undef C2
-    return hipErrorInvalidValue;
-}
-
-hipError_t blas_add_zero(const Field &xhi, const Field &xs, int Vh, const int *active, int nact,
-                         hipStream_t s)
-{
-    if (nact == 0) return hipSuccess;
-    if (xhi.sp != SP_F64) return hipErrorInvalidValue;
-    dim3 gr = grid_of(Vh, xhi.nsub, nact);
-    if (xs.sp == SP_F32)
-        hipLaunchKernelGGL(k_add_zero<SP_F32>, gr, dim3(kBlock), 0, s, fa(xhi), fa(xs), Vh, xhi.nsub, active);
-    else if (xs.sp == SP_F64)
-        hipLaunchKernelGGL(k_add_zero<SP_F64>, gr, dim3(kBlock), 0, s, fa(xhi), fa(xs), Vh, xhi.nsub, active);
-    else
-        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t blas_resid(const Field &r, const Field &b, const Field &Ap, int Vh, const int *active,
-                      int nact, double *partial, int pstride, hipStream_t s)
+hipError_t blas_set_coefs(double *c1, double *c2, const int *ids, const double *kappa, int n, hipStream_t s)
 {
-    if (nact == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_resid, grid_of(Vh, r.nsub, nact), dim3(kBlock), 0, s, fa(r), fa(b), fa(Ap), Vh, r.nsub, active, partial, pstride);
+    for (int b = 0; b < n; b += 32) {
+        CoefList l;
+        l.n = n - b < 32 ? n - b : 32;
+        for (int q = 0; q < 32; q++) {
+            l.id[q] = q < l.n ? ids[b + q] : 0;
+            l.kappa[q] = q < l.n ? kappa[b + q] : 0.0;
+        }
+        hipLaunchKernelGGL(k_set_coefs, dim3(1), dim3(64), 0, s, c1, c2, l);
+    }
     return hipGetLastError();
 }
 
-hipError_t blas_zero(const Field &a, int Vh, const int *active, int nact, hipStream_t s)
+hipError_t blas_cg_init(bool fresh, const Field &b, const Field &x, const Field &r, const Field &rs, const Field &xs,
+                        const Field &p, int Vh, const int *active, int nact, double *partial, int pstride,
+                        hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
-#define F(SP) hipLaunchKernelGGL(k_zero<SP>, grid_of(Vh, a.nsub, nact), dim3(kBlock), 0, s, fa(a), Vh, a.nsub, active)
-    SP_SWITCH(a.sp, F)
-#undef F
-    return hipGetLastError();
-}
-
-hipError_t blas_cdot(const Field &a, const Field &b, int Vh, const int *active, int nact,
-                     double *pre, double *pim, int pstride, hipStream_t s)
-{
-    if (nact == 0) return hipSuccess;
-    if (a.sp != b.sp) return hipErrorInvalidValue;
-#define F(SP) hipLaunchKernelGGL(k_cdot<SP>, grid_of(Vh, a.nsub, nact), dim3(kBlock), 0, s, fa(a), fa(b), Vh, a.nsub, active, pre, pim, pstride)
-    SP_SWITCH(a.sp, F)
-#undef F
-    return hipGetLastError();
-}
-
-hipError_t blas_orth(const Field &p, const Field &r, const double *dre, const double *dim,
-                     const double *rr, int Vh, const int *active, int nact, hipStream_t s)
-{
-    if (nact == 0) return hipSuccess;
-    if (p.sp != r.sp) return hipErrorInvalidValue;
-#define F(SP) hipLaunchKernelGGL(k_orth<SP>, grid_of(Vh, p.nsub, nact), dim3(kBlock), 0, s, fa(p), fa(r), dre, dim, rr, Vh, p.nsub, active)
+    const dim3 gr = grid_of(Vh, b.nsub, nact);
+#define F(SP)                                                                                                     \
+    if (fresh)                                                                                                    \
+        hipLaunchKernelGGL((k_cg_init<SP, true>), gr, dim3(kBlock), 0, s, fa(b), fa(x), fa(r), fa(rs), fa(xs), fa(p), \
+                           Vh, b.nsub, active, partial, pstride);                                                 \
+    else                                                                                                          \
+        hipLaunchKernelGGL((k_cg_init<SP, false>), gr, dim3(kBlock), 0, s, fa(b), fa(x), fa(r), fa(rs), fa(xs), fa(p), \
+                           Vh, b.nsub, active, partial, pstride)
     SP_SWITCH(p.sp, F)
 #undef F
     return hipGetLastError();
 }
 
-hipError_t blas_axpy_const(const Field &p, const Field &r, double a, int Vh, const int *active,
-                           int nact, hipStream_t s)
+hipError_t blas_ru_begin(const Field &p, const Field &r, const Field &x, const Field *xs, const double *rr, double *rr_s,
+                         int Vh, const int *active, int nact, hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
-    if (p.sp != r.sp) return hipErrorInvalidValue;
-#define F(SP) hipLaunchKernelGGL(k_axpy_const<SP>, grid_of(Vh, p.nsub, nact), dim3(kBlock), 0, s, fa(p), fa(r), a, Vh, p.nsub, active)
+    if (p.sp != r.sp || (xs && xs->sp != SP_F32)) return hipErrorInvalidValue;
+    const dim3 gr = grid_of(Vh, p.nsub, nact);
+#define F(SP)                                                                                                        \
+    if (xs)                                                                                                          \
+        hipLaunchKernelGGL((k_ru_begin<SP, SP_F32, true>), gr, dim3(kBlock), 0, s, fa(p), fa(r), fa(x), fa(*xs), rr, rr_s, \
+                           Vh, p.nsub, active);                                                                      \
+    else                                                                                                             \
+        hipLaunchKernelGGL((k_ru_begin<SP, SP_F32, false>), gr, dim3(kBlock), 0, s, fa(p), fa(r), fa(x), fa(x), rr, rr_s, \
+                           Vh, p.nsub, active)
     SP_SWITCH(p.sp, F)
 #undef F
     return hipGetLastError();
 }
 
-hipError_t blas_xpay_ratio(const Field &p, const Field &r, const double *num, const double *den, int Vh,
-                           const int *active, int nact, hipStream_t s)
+hipError_t blas_ru_mid(const Field &r64, const Field &r, bool sloppy, const Field &p, int Vh, const int *active,
+                       int nact, double *pre, double *pim, int pstride, hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
     if (p.sp != r.sp) return hipErrorInvalidValue;
-#define F(SP) hipLaunchKernelGGL(k_xpay_ratio<SP>, grid_of(Vh, p.nsub, nact), dim3(kBlock), 0, s, fa(p), fa(r), num, den, Vh, p.nsub, active)
+    const dim3 gr = grid_of(Vh, p.nsub, nact);
+#define F(SP)                                                                                                     \
+    if (sloppy)                                                                                                   \
+        hipLaunchKernelGGL((k_ru_mid<SP, true>), gr, dim3(kBlock), 0, s, fa(r64), fa(r), fa(p), Vh, p.nsub, active, pre, \
+                           pim, pstride);                                                                         \
+    else                                                                                                          \
+        hipLaunchKernelGGL((k_ru_mid<SP, false>), gr, dim3(kBlock), 0, s, fa(r64), fa(r), fa(p), Vh, p.nsub, active, pre, \
+                           pim, pstride)
+    SP_SWITCH(p.sp, F)
+#undef F
+    return hipGetLastError();
+}
+
+hipError_t blas_ru_sums(const double *prr, int nwr, const double *pre, const double *pim, int nw, int pstride,
+                        double *rr, double *hout, double *dre, double *dim, const int *active, int nact,
+                        hipStream_t s)
+{
+    if (nact == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_ru_sums, dim3(3, nact), dim3(kBlock), 0, s, prr, nwr, pre, pim, nw, pstride, rr, hout, dre, dim,
+                       active);
+    return hipGetLastError();
+}
+
+hipError_t blas_ru_end(const Field &p, const Field &r, const double *dre, const double *dim, const double *rr,
+                       const double *rr_s, int Vh, const int *active, int nact, hipStream_t s)
+{
+    if (nact == 0) return hipSuccess;
+    if (p.sp != r.sp) return hipErrorInvalidValue;
+#define F(SP) hipLaunchKernelGGL(k_ru_end<SP>, grid_of(Vh, p.nsub, nact), dim3(kBlock), 0, s, fa(p), fa(r), dre, dim, rr, rr_s, Vh, p.nsub, active)
     SP_SWITCH(p.sp, F)
 #undef F
     return hipGetLastError();
 }
 
 hipError_t blas_finalize(const double *partial, int pstride, int nw, const int *active, int nact,
-                         int mode, double *rr, double *alpha, double *beta, double *out,
+                         int mode, double *rr, double *alpha, double *beta, double *out, double *hout,
                          hipStream_t s)
 {
     if (nact == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize, dim3(nact), dim3(kBlock), 0, s, partial, pstride, nw, active, mode, rr, alpha, beta, out);
+    hipLaunchKernelGGL(k_finalize, dim3(nact), dim3(kBlock), 0, s, partial, pstride, nw, active, mode, rr, alpha, beta, out, hout);
     return hipGetLastError();
 }
 

@@ -207,6 +207,8 @@ __global__ void __launch_bounds__(2 * kSmallSites) k_cg_small(SmallArgs a)
         a.alpha[rid] = alpha;
         a.beta[rid] = beta;
         a.it_out[rid] = it;
+        a.hout[rid] = rr;
+        __threadfence_system();
     }
 }
 

@@ -226,6 +226,7 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
     a.x_rs = sw.x.rs;
     a.coef = sw.coef;
     a.r = sw.r.base;
+    a.rsrc = sw.rsrc ? sw.rsrc : sw.r.base;
     a.r_rs = sw.r.rs;
     a.alpha = sw.alpha;
     a.active = sw.active;
@@ -526,7 +527,7 @@ wd_status wd_destroy(wd_ctx *c)
     if (c->links16) (void)hipFree(c->links16);
     if (c->links32r) (void)hipFree(c->links32r);
     if (c->links8) (void)hipFree(c->links8);
-    for (int k = 0; k < 2; k++)
+    for (int k = 0; k < 3; k++)
         if (c->pinned[k]) (void)hipHostFree(c->pinned[k]);
     for (auto &e : c->events) {
         (void)hipEventDestroy(e.first);

@@ -19,6 +19,10 @@
 //              sums) -- the last sweep of Mhat^dag Mhat p fused with the CG
 //              residual update (the solution is advanced from the search
 //              directions of several iterations at once, by the p update).
+//              With r's source another field and alpha = 1 it forms the true
+//              residual r = b - Ap of a reliable update.
+//              With r's source another field and alpha = 1 it forms the true
+//              residual r = b - Ap of a reliable update.
 // Partial sums cover 16 consecutive sites of one RHS and are formed with the
 // same pairing tree for every (NR, RL, block) choice, so every launch shape
 // gives bitwise-identical vectors and norms.
@@ -354,10 +358,10 @@ __device__ __forceinline__ void dslash_epilogue(const DslashArgs &a, int i, bool
                 SpinorIO<SP>::template store<true>(a.out + rid[r] * a.out_rs, cs, i, xv);
             } else {
                 const real cf = (real)a.coef[rid[r]];
-                const real al = (real)a.alpha[rid[r]];
+                const real al = a.alpha ? (real)a.alpha[rid[r]] : (real)1;
                 real ap[24], rv_[24];
                 SpinorIO<SP>::template load<true>(a.x + rid[r] * a.x_rs, cs, i, ap);
-                SpinorIO<SP>::template load<true>(a.r + rid[r] * a.r_rs, cs, i, rv_);
+                SpinorIO<SP>::template load<true>(a.rsrc + rid[r] * a.r_rs, cs, i, rv_);
 #pragma unroll
                 for (int k = 0; k < 24; k++) {
                     ap[k] = fmaT(cf, acc[r][k], ap[k]);

@@ -98,12 +98,16 @@ struct BatchSolver {
     double *rr_s = nullptr;  // recursive |r|^2 saved at a reliable update
     double *rr_b = nullptr;  // |r|^2 after every other iteration of a step (see iterate)
     double *ahist = nullptr; // alpha of the iterations since the last flush, [kRing][cap]
-    double *hbuf = nullptr;  // pinned, cap doubles and cap ints
-    int *ibuf = nullptr;     // the ints of it
+    // pinned memory the kernels write results to: |r|^2 and |b|^2 of every slot,
+    // and the iterations of small_steps
+    double *hbuf = nullptr, *hbb = nullptr;
+    int *ibuf = nullptr;
+    bool own_hbuf = false;  // (a session's; the one-shot solver's is the context's)
     int *act = nullptr, *act64 = nullptr, *lst = nullptr;  // device id lists
     std::vector<int> state, iters, iters64, rus, status, last_ru, stall, active, active64;
     std::vector<double> bbh, maxrr, best, tres, kap;
     bool trace = false;
+    bool one_shot = false;  // wd_cg_solve: state in the context's workspaces, reused across calls
     bool fold = true;  // alpha finalized inside sweep 3 (else by its own kernel)
 
     std::string nm(const char *s) const { return pre + s; }
@@ -120,7 +124,7 @@ struct BatchSolver {
         nsub = p.eo ? 1 : 2;
         Vh = (int)c->Vh;
         nw1 = ngroups_of(Vh);
-        pstride = 2 * nw1 + 1;
+        pstride = (p.eo ? 2 : 4) * nw1 + 1;  // (a reliable update holds two sums' partials side by side)
         nwF = p.eo ? nw1 : ngroups_of(2 * Vh);
         nwD = p.eo ? nw1 : 2 * nw1;
         WD_TRY(bind(capacity));
@@ -199,11 +203,25 @@ struct BatchSolver {
                 lane_s.Pr.push_back(f);
             }
         if (!mixed) lane_s = lane_d;
-        if (hbuf) (void)hipHostFree(hbuf);
-        hbuf = nullptr;
-        WD_HIP(hipHostMalloc((void **)&hbuf, (sizeof(double) + sizeof(int)) * cap, hipHostMallocDefault));
-        ibuf = (int *)(hbuf + cap);
+        free_hbuf();
+        const size_t hbytes = (2 * sizeof(double) + sizeof(int)) * cap;
+        if (one_shot) {
+            WD_TRY(pinned_get(c, 2, hbytes, &vp));
+            hbuf = (double *)vp;
+        } else {
+            WD_HIP(hipHostMalloc((void **)&hbuf, hbytes, hipHostMallocDefault));
+            own_hbuf = true;
+        }
+        hbb = hbuf + cap;
+        ibuf = (int *)(hbb + cap);
         return WD_OK;
+    }
+
+    void free_hbuf()
+    {
+        if (own_hbuf) (void)hipHostFree(hbuf);
+        hbuf = nullptr;
+        own_hbuf = false;
     }
 
     // Change the number of slots to ncap, keeping the state of slots below
@@ -281,15 +299,14 @@ struct BatchSolver {
         best.resize(cap, 0.0);
         tres.resize(cap, 0.0);
         kap.resize(cap, 0.0);
-        WD_TRY(upload_list(active, act));
-        WD_TRY(upload_list(active64, act64));
+        WD_TRY(set_list(active, act));
+        WD_TRY(set_list(active64, act64));
         return WD_OK;
     }
 
     void release()
     {
-        if (hbuf) (void)hipHostFree(hbuf);
-        hbuf = nullptr;
+        free_hbuf();
         for (auto it = c->ws.begin(); it != c->ws.end();) {
             if (it->first.compare(0, pre.size(), pre) == 0) {
                 (void)hipFree(it->second.first);
@@ -300,40 +317,23 @@ struct BatchSolver {
         }
     }
 
-    wd_status upload_list(const std::vector<int> &v, int *dev)
+    wd_status set_list(const std::vector<int> &v, int *dev)
     {
-        if (v.empty()) return WD_OK;
-        void *h;
-        WD_HIP(hipStreamSynchronize(c->stream));
-        WD_TRY(pinned_get(c, 0, sizeof(int) * v.size(), &h));
-        std::memcpy(h, v.data(), sizeof(int) * v.size());
-        WD_HIP(hipMemcpyAsync(dev, h, sizeof(int) * v.size(), hipMemcpyHostToDevice, c->stream));
-        WD_HIP(hipStreamSynchronize(c->stream));
+        HIPCHK(blas_set_ids(dev, v.data(), (int)v.size(), c->stream));
         return WD_OK;
     }
 
-    wd_status upload_coefs()
-    {
-        std::vector<double> h(2 * cap);
-        for (int j = 0; j < cap; j++) {
-            h[j] = -kap[j];
-            h[cap + j] = -kap[j] * kap[j];
-        }
-        void *hp;
-        WD_HIP(hipStreamSynchronize(c->stream));
-        WD_TRY(pinned_get(c, 0, sizeof(double) * 2 * cap, &hp));
-        std::memcpy(hp, h.data(), sizeof(double) * 2 * cap);
-        WD_HIP(hipMemcpyAsync(coef1, hp, sizeof(double) * 2 * cap, hipMemcpyHostToDevice, c->stream));
-        WD_HIP(hipStreamSynchronize(c->stream));
-        return WD_OK;
-    }
+    // The last sweeps of A in as out = A in, or as the true residual r64 = b64 -
+    // A in with the partials of |r64|^2 (nwD of them).
+    enum Last { APPLY, RESID };
 
-    // out = A in (FP64 or sloppy) for the listed RHS, temporaries to64, te64
-    wd_status apply_A(int spp, int lkk, const Field &in, const Field &out, const int *ids, int n, bool norm)
+    // A in (FP64) for the listed RHS, temporaries to64, te64; norm: the partials
+    // of |M in|^2 (full-lattice solver).
+    wd_status apply_A(const Field &in, const Field &out, const int *ids, int n, bool norm, Last last)
     {
         Sweep sw;
-        sw.sp = spp;
-        sw.lk = lkk;
+        sw.sp = SP_F64;
+        sw.lk = c->lk64;
         sw.active = ids;
         sw.nact = n;
         if (p.eo) {
@@ -341,28 +341,35 @@ struct BatchSolver {
             sw.P = 1; sw.dag = 0; sw.epi = EPI_PLAIN; sw.in = in; sw.out = to64;
             WD_TRY(run_sweep(c, sw, nullptr));
             sw.P = 0; sw.epi = EPI_XPAY; sw.in = to64; sw.x = in; sw.out = te64;
-            sw.partial = norm ? partial : nullptr; sw.pstride = pstride; sw.pw_off = 0;
             WD_TRY(run_sweep(c, sw, nullptr));
-            sw.partial = nullptr;
             sw.P = 1; sw.dag = 1; sw.epi = EPI_PLAIN; sw.in = te64; sw.out = to64;
             WD_TRY(run_sweep(c, sw, nullptr));
-            sw.P = 0; sw.epi = EPI_XPAY; sw.in = to64; sw.x = te64; sw.out = out;
+            sw.P = 0; sw.in = to64; sw.x = te64;
+            if (last == RESID) {
+                sw.epi = EPI_CGUPD; sw.r = r64; sw.rsrc = b64.base;
+                sw.partial = partial; sw.pstride = pstride; sw.pw_off = 0;
+            } else {
+                sw.epi = EPI_XPAY; sw.out = out;
+            }
             WD_TRY(run_sweep(c, sw, nullptr));
         } else {
             const Field &T = te64;
             sw.coef = coef1;
-            sw.epi = EPI_XPAY;
+            sw.pstride = pstride;
             for (int pass = 0; pass < 2; pass++) {
                 const Field &src = pass ? T : in;
                 const Field &dst = pass ? out : T;
+                const bool res = pass == 1 && last == RESID;
                 sw.dag = pass;
+                sw.epi = res ? EPI_CGUPD : EPI_XPAY;
                 for (int P = 0; P < 2; P++) {
                     sw.P = P;
                     sw.in = sub_view(src, 1 - P);
                     sw.x = sub_view(src, P);
                     sw.out = sub_view(dst, P);
-                    sw.partial = (norm && pass == 0) ? partial : nullptr;
-                    sw.pstride = pstride;
+                    sw.r = sub_view(r64, P);
+                    sw.rsrc = res ? sub_view(b64, P).base : nullptr;
+                    sw.partial = ((norm && pass == 0) || res) ? partial : nullptr;
                     sw.pw_off = P * nw1;
                     WD_TRY(run_sweep(c, sw, nullptr));
                 }
@@ -416,7 +423,7 @@ struct BatchSolver {
                 sw.fin_rr = rr; sw.fin_alpha = alpha; sw.fin_out = ahist + (size_t)j * cap;
             } else {
                 HIPCHK(blas_finalize(partial, pstride, nwD, ids, n, FIN_ALPHA, rr, alpha, beta,
-                                     ahist + (size_t)j * cap, s));
+                                     ahist + (size_t)j * cap, nullptr, s));
             }
             WD_TRY(run_sweep(c, sw, nullptr));
             sw.fin_partial = nullptr;
@@ -430,8 +437,10 @@ struct BatchSolver {
                 bf.nw = nw1;
                 bf.rr_in = rr;
                 bf.rr_out = rr_out;
+                bf.hout = last ? hbuf : nullptr;
             } else {
-                HIPCHK(blas_finalize(partial, pstride, nw1, ids, n, FIN_BETA, rr, alpha, beta, nullptr, s));
+                HIPCHK(blas_finalize(partial, pstride, nw1, ids, n, FIN_BETA, rr, alpha, beta, nullptr,
+                                     last ? hbuf : nullptr, s));
             }
             if (flush)
                 HIPCHK(blas_p_update_ring(L.Pr.data(), j + 1, L.Pr[0], L.R, bf, beta, true, L.X, ahist, cap, Vh, ids,
@@ -440,10 +449,11 @@ struct BatchSolver {
                 HIPCHK(blas_p_update_ring(&L.Pr[j], 1, L.Pr[j + 1], L.R, bf, beta, false, L.X, ahist, cap, Vh, ids,
                                           n, s));
         } else {
-            WD_TRY(apply_A(L.sp, L.lk, L.P, Ap64, ids, n, true));
-            HIPCHK(blas_finalize(partial, pstride, nwD, ids, n, FIN_ALPHA, rr, alpha, beta, nullptr, s));
+            WD_TRY(apply_A(L.P, Ap64, ids, n, true, APPLY));
+            HIPCHK(blas_finalize(partial, pstride, nwD, ids, n, FIN_ALPHA, rr, alpha, beta, nullptr, nullptr, s));
             HIPCHK(blas_cg_update(L.X, L.P, L.R, Ap64, alpha, Vh, ids, n, partial, pstride, s));
-            HIPCHK(blas_finalize(partial, pstride, nwF, ids, n, FIN_BETA, rr, alpha, beta, nullptr, s));
+            HIPCHK(blas_finalize(partial, pstride, nwF, ids, n, FIN_BETA, rr, alpha, beta, nullptr,
+                                 last ? hbuf : nullptr, s));
             HIPCHK(blas_p_update(L.P, L.R, beta, Vh, ids, n, s));
         }
         return WD_OK;
@@ -477,45 +487,45 @@ struct BatchSolver {
         if ((int)slots.size() < n) return set_error(WD_ERR_OOM, "%d free slots, %d requested", (int)slots.size(), n);
         const hipStream_t s = c->stream;
         const long long site_doubles = (long long)24 * Vh * nsub;
-        for (int q = 0; q < n; q++) {
-            Field v = b64;
-            v.base = b64.base + slots[q] * b64.rs;
-            HIPCHK(pack_spinor(phi + q * site_doubles, v, 1, p.eo ? 0 : 1, c->g, s));
-            kap[slots[q]] = kappa[q];
-        }
-        WD_TRY(upload_coefs());
-        WD_TRY(upload_list(slots, lst));
-        HIPCHK(blas_norm(b64, Vh, lst, n, partial, pstride, s));
-        HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_STORE, rr, alpha, beta, bb, s));
+        // pack src's n fields into the slots' rows of f, a launch per run of
+        // consecutive slots
+        auto pack = [&](const double *src, const Field &f) -> wd_status {
+            for (int q = 0; q < n;) {
+                int e = q + 1;
+                while (e < n && slots[e] == slots[e - 1] + 1) e++;
+                Field v = f;
+                v.base = f.base + slots[q] * f.rs;
+                HIPCHK(pack_spinor(src + q * site_doubles, v, e - q, p.eo ? 0 : 1, c->g, s));
+                q = e;
+            }
+            return WD_OK;
+        };
+        WD_TRY(pack(phi, b64));
+        for (int q = 0; q < n; q++) kap[slots[q]] = kappa[q];
+        HIPCHK(blas_set_coefs(coef1, coef2, slots.data(), kappa, n, s));
+        WD_TRY(set_list(slots, lst));
         if (x0) {
             // start from x0: x = x0, r = b - A x0 in FP64, rr = |r|^2
-            for (int q = 0; q < n; q++) {
-                Field v = x64;
-                v.base = x64.base + slots[q] * x64.rs;
-                HIPCHK(pack_spinor(x0 + q * site_doubles, v, 1, p.eo ? 0 : 1, c->g, s));
-            }
-            WD_TRY(apply_A(SP_F64, c->lk64, x64, Ap64, lst, n, false));
-            HIPCHK(blas_resid(r64, b64, Ap64, Vh, lst, n, partial, pstride, s));
+            HIPCHK(blas_norm(b64, Vh, lst, n, partial, pstride, s));
+            HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_STORE, rr, alpha, beta, bb, hbb, s));
+            WD_TRY(pack(x0, x64));
+            WD_TRY(apply_A(x64, Ap64, lst, n, false, RESID));
+            HIPCHK(blas_finalize(partial, pstride, nwD, lst, n, FIN_RR, rr, alpha, beta, nullptr, hbuf, s));
+            HIPCHK(blas_cg_init(false, b64, x64, r64, rs, xs, lane_s.P, Vh, lst, n, partial, pstride, s));
         } else {
-            HIPCHK(blas_zero(x64, Vh, lst, n, s));
-            HIPCHK(blas_copy(r64, b64, Vh, lst, n, s));
+            HIPCHK(blas_cg_init(true, b64, x64, r64, rs, xs, lane_s.P, Vh, lst, n, partial, pstride, s));
+            HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_RR, rr, alpha, beta, bb, hbuf, s));
         }
-        HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_RR, rr, alpha, beta, nullptr, s));
-        if (mixed) {
-            HIPCHK(blas_copy(rs, r64, Vh, lst, n, s));
-            HIPCHK(blas_zero(xs, Vh, lst, n, s));
-        }
-        HIPCHK(blas_copy(lane_s.P, lane_s.R, Vh, lst, n, s));
+        HIPCHK(hipStreamSynchronize(s));
         std::vector<double> rr0(cap, 0.0);
-        HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (int q = 0; q < n; q++) rr0[slots[q]] = hbuf[slots[q]];
-        HIPCHK(hipMemcpyAsync(hbuf, bb, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        for (int q = 0; q < n; q++) {
+            rr0[slots[q]] = hbuf[slots[q]];
+            if (!x0) hbb[slots[q]] = hbuf[slots[q]];
+        }
         const double tol2 = p.tol * p.tol;
         for (int q = 0; q < n; q++) {
             const int j = slots[q];
-            bbh[j] = hbuf[j];
+            bbh[j] = hbb[j];
             iters[j] = iters64[j] = 0;
             rus[j] = 0;
             last_ru[j] = 0;
@@ -541,7 +551,7 @@ struct BatchSolver {
             if (slots_out) slots_out[q] = j;
         }
         std::sort(active.begin(), active.end());
-        WD_TRY(upload_list(active, act));
+        WD_TRY(set_list(active, act));
         return WD_OK;
     }
 
@@ -557,21 +567,15 @@ struct BatchSolver {
     {
         if (ids.empty()) return WD_OK;
         const hipStream_t s = c->stream;
-        WD_TRY(upload_list(ids, lst));
+        WD_TRY(set_list(ids, lst));
         const int n = (int)ids.size();
-        HIPCHK(hipMemcpyAsync(rr_s, rr, sizeof(double) * cap, hipMemcpyDeviceToDevice, s));
-        HIPCHK(blas_axpy_const(L.P, L.R, -1.0, Vh, lst, n, s));
-        if (L.sloppy) HIPCHK(blas_add_zero(x64, L.X, Vh, lst, n, s));
-        WD_TRY(apply_A(SP_F64, c->lk64, x64, Ap64, lst, n, false));
-        HIPCHK(blas_resid(r64, b64, Ap64, Vh, lst, n, partial, pstride, s));
-        HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_RR, rr, alpha, beta, nullptr, s));
-        if (L.sloppy) HIPCHK(blas_copy(L.R, r64, Vh, lst, n, s));
-        HIPCHK(blas_cdot(L.R, L.P, Vh, lst, n, partial, partial2, pstride, s));
-        HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_STORE, rr, alpha, beta, dre, s));
-        HIPCHK(blas_finalize(partial2, pstride, nwF, lst, n, FIN_STORE, rr, alpha, beta, dim, s));
-        HIPCHK(blas_orth(L.P, L.R, dre, dim, rr, Vh, lst, n, s));
-        HIPCHK(blas_xpay_ratio(L.P, L.R, rr, rr_s, Vh, lst, n, s));
-        HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
+        HIPCHK(blas_ru_begin(L.P, L.R, x64, L.sloppy ? &L.X : nullptr, rr, rr_s, Vh, lst, n, s));
+        WD_TRY(apply_A(x64, Ap64, lst, n, false, RESID));
+        // (|r|^2's nwD partials are followed by Re <r, p>'s, so one launch sums all)
+        double *const pre = partial + nwD;
+        HIPCHK(blas_ru_mid(r64, L.R, L.sloppy, L.P, Vh, lst, n, pre, partial2, pstride, s));
+        HIPCHK(blas_ru_sums(partial, nwD, pre, partial2, nwF, pstride, rr, hbuf, dre, dim, lst, n, s));
+        HIPCHK(blas_ru_end(L.P, L.R, dre, dim, rr, rr_s, Vh, lst, n, s));
         HIPCHK(hipStreamSynchronize(s));
         for (int j : ids) rrh[j] = hbuf[j];
         return WD_OK;
@@ -604,7 +608,7 @@ struct BatchSolver {
                               (const void *)c->links32r, (const void *)c->links8, (const void *)coef1,
                               (const void *)coef2,
                               (const void *)rr, (const void *)alpha, (const void *)beta, (const void *)partial,
-                              (const void *)act, (const void *)act64, (const void *)ahist})
+                              (const void *)act, (const void *)act64, (const void *)ahist, (const void *)hbuf})
             add((unsigned long long)(uintptr_t)q);
         add((unsigned long long)cap);
         for (const Lane *L : {&lane_s, &lane_d}) {
@@ -679,7 +683,8 @@ struct BatchSolver {
         a.rr = rr;
         a.alpha = alpha;
         a.beta = beta;
-        a.it_out = act64;  // (an FP64 solve has no second lane: its id list is free)
+        a.it_out = ibuf;
+        a.hout = hbuf;
         a.tol2 = p.tol * p.tol;
         a.k = k;
         a.maxiter = p.maxiter;
@@ -692,8 +697,6 @@ struct BatchSolver {
             }
             HIPCHK(cg_small_launch(a, n, c->lk64, p.eo != 0, s));
         }
-        HIPCHK(hipMemcpyAsync(ibuf, act64, sizeof(int) * cap, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         for (int j : active) iters[j] = ibuf[j];
         return checks();
@@ -715,7 +718,6 @@ struct BatchSolver {
             iters[j] += k;
             iters64[j] += k;
         }
-        HIPCHK(hipMemcpyAsync(hbuf, rr, sizeof(double) * cap, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         return checks();
     }
@@ -799,12 +801,12 @@ struct BatchSolver {
         // restarts p = r; escalated slots start FP64 CG from p64 = r64 (the
         // true residual of their current x64)
         if (!restart[0].empty()) {
-            WD_TRY(upload_list(restart[0], lst));
+            WD_TRY(set_list(restart[0], lst));
             HIPCHK(blas_copy(lane_s.P, lane_s.R, Vh, lst, (int)restart[0].size(), s));
         }
         for (int j : escalate) restart[1].push_back(j);
         if (!restart[1].empty()) {
-            WD_TRY(upload_list(restart[1], lst));
+            WD_TRY(set_list(restart[1], lst));
             HIPCHK(blas_copy(p64, r64, Vh, lst, (int)restart[1].size(), s));
         }
         if (trace) {
@@ -816,11 +818,11 @@ struct BatchSolver {
         std::sort(keep[1].begin(), keep[1].end());
         if (keep[0] != active) {
             active.swap(keep[0]);
-            WD_TRY(upload_list(active, act));
+            WD_TRY(set_list(active, act));
         }
         if (keep[1] != active64) {
             active64.swap(keep[1]);
-            WD_TRY(upload_list(active64, act64));
+            WD_TRY(set_list(active64, act64));
         }
         return WD_OK;
     }
@@ -890,15 +892,9 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     c->use_tuned = p.tuned != 0;
 
     // the one-shot solver keeps its state in the context's "cg_" workspaces,
-    // reused across calls; only its pinned buffer is released here
+    // reused across calls
     BatchSolver bs;
-    struct PinnedScope {
-        BatchSolver &b;
-        ~PinnedScope()
-        {
-            if (b.hbuf) (void)hipHostFree(b.hbuf);
-        }
-    } pscope{bs};
+    bs.one_shot = true;
     WD_TRY(bs.init(c, nrhs, p, "cg_"));
     WD_TRY(bs.add(phi, nrhs, kappa, nullptr, p.initial_guess ? x : nullptr));
     int it = 0;
@@ -914,7 +910,10 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
             bs.status[j] = WD_ERR_NOCONV;
             bs.state[j] = SLOT_DONE;
         }
-    for (int j = 0; j < nrhs; j++) WD_TRY(bs.unpack(j, x + (size_t)j * 24 * c->Vh * bs.nsub));
+    {  // (slots 0 .. nrhs-1 in order)
+        const hipError_t e = unpack_spinor(bs.x64, x, nrhs, p.eo ? 0 : 1, c->g, c->stream);
+        if (e != hipSuccess) return set_error(WD_ERR_HIP, "unpack: %s", hipGetErrorString(e));
+    }
     WD_HIP(hipStreamSynchronize(c->stream));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     wd_status ret = WD_OK;

@@ -56,9 +56,10 @@ struct DslashArgs {
     const char *x;         // xpay: out = x + coef*D in
     long long x_rs;
     const double *coef;    // [rid]
-    char *r;               // CG update: r -= alpha (x + coef*D in)
+    char *r;               // CG update: r = rsrc - alpha (x + coef*D in)
+    const char *rsrc;      // (r itself in an iteration, b for a true residual; stride r_rs too)
     long long r_rs;
-    const double *alpha;   // [rid]
+    const double *alpha;   // [rid], or null: 1
     const int *active;     // RHS ids processed by this launch
     int nact;
     int G;                 // RHS groups of RL*NR per tile
@@ -164,7 +165,8 @@ struct SmallArgs {
     Field p, r, x;  // FP64
     const double *coef = nullptr, *bb = nullptr;  // [rid]
     double *rr = nullptr, *alpha = nullptr, *beta = nullptr;
-    int *it_out = nullptr;  // [rid] iterations done
+    int *it_out = nullptr;     // pinned host memory: [rid] iterations done
+    double *hout = nullptr;    // pinned host memory: [rid] |r|^2
     double tol2 = 0.0;
     int k = 1, maxiter = 0, max_steps = 1;
     int rid[kSmallBatch] = {}, it[kSmallBatch] = {};  // and the iterations each has behind it
@@ -173,6 +175,7 @@ bool cg_small_ok(const Geom &g, int nsub);
 hipError_t cg_small_launch(const SmallArgs &a, int nrhs, int lk, bool eo, hipStream_t s);
 
 // BLAS-1 / reductions (blas.hip).  All take an active-RHS list.
+// FIN_STORE out = sum; FIN_ALPHA, FIN_BETA the CG scalars; FIN_RR rr = sum, and out = sum where out is given
 enum { FIN_STORE = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_RR = 3 };
 hipError_t blas_norm(const Field &a, int Vh, const int *active, int nact, double *partial,
                      int pstride, hipStream_t s);
@@ -191,6 +194,7 @@ struct BetaFold {
     int pstride = 0, nw = 0;
     const double *rr_in = nullptr;
     double *rr_out = nullptr;
+    double *hout = nullptr;  // pinned host memory: receives the sum too (may be null)
 };
 hipError_t blas_p_update_ring(const Field *p, int m, const Field &pdst, const Field &r, const BetaFold &bf,
                               double *beta, bool flush, const Field &x, const double *ahist, int ahs, int Vh,
@@ -200,21 +204,33 @@ hipError_t blas_cg_update(const Field &x, const Field &p, const Field &r, const 
                           double *partial, int pstride, hipStream_t s);
 hipError_t blas_copy(const Field &dst, const Field &src, int Vh, const int *active, int nact,
                      hipStream_t s);
-hipError_t blas_add_zero(const Field &xhi, const Field &xs, int Vh, const int *active, int nact,
-                         hipStream_t s);
-hipError_t blas_resid(const Field &r, const Field &b, const Field &Ap, int Vh, const int *active,
-                      int nact, double *partial, int pstride, hipStream_t s);
-hipError_t blas_zero(const Field &a, int Vh, const int *active, int nact, hipStream_t s);
-hipError_t blas_cdot(const Field &a, const Field &b, int Vh, const int *active, int nact,
-                     double *pre, double *pim, int pstride, hipStream_t s);
-hipError_t blas_orth(const Field &p, const Field &r, const double *dre, const double *dim,
-                     const double *rr, int Vh, const int *active, int nact, hipStream_t s);
-hipError_t blas_axpy_const(const Field &p, const Field &r, double a, int Vh, const int *active,
-                           int nact, hipStream_t s);
-hipError_t blas_xpay_ratio(const Field &p, const Field &r, const double *num, const double *den, int Vh,
-                           const int *active, int nact, hipStream_t s);
+// Lists written on the stream without a copy from the host (the values travel
+// as kernel arguments).
+hipError_t blas_set_ids(int *dst, const int *ids, int n, hipStream_t s);
+// c1[id] = -kappa, c2[id] = -kappa^2
+hipError_t blas_set_coefs(double *c1, double *c2, const int *ids, const double *kappa, int n, hipStream_t s);
+// The CG state of right-hand sides whose residual is r: fresh: x = 0, r = b and
+// the partials of |b|^2; and in a mixed solve (sloppy p.sp) rs = r, xs = 0; p = r.
+hipError_t blas_cg_init(bool fresh, const Field &b, const Field &x, const Field &r, const Field &rs, const Field &xs,
+                        const Field &p, int Vh, const int *active, int nact, double *partial, int pstride,
+                        hipStream_t s);
+// A reliable update before, between and after the FP64 sweeps:
+//   begin: p -= r; sloppy: x += xs, xs = 0; rr_s = rr
+//   mid:   sloppy: rs = r; the partials of <rs, p> (real in pre, imaginary in pim)
+//   sums:  rr (also to hout), dre and dim of their partials
+//   end:   p -= (<r, p> / rr) r, then p = r + (rr / rr_s) p
+hipError_t blas_ru_begin(const Field &p, const Field &r, const Field &x, const Field *xs, const double *rr, double *rr_s,
+                         int Vh, const int *active, int nact, hipStream_t s);
+hipError_t blas_ru_mid(const Field &r64, const Field &r, bool sloppy, const Field &p, int Vh, const int *active,
+                       int nact, double *pre, double *pim, int pstride, hipStream_t s);
+hipError_t blas_ru_sums(const double *prr, int nwr, const double *pre, const double *pim, int nw, int pstride,
+                        double *rr, double *hout, double *dre, double *dim, const int *active, int nact,
+                        hipStream_t s);
+hipError_t blas_ru_end(const Field &p, const Field &r, const double *dre, const double *dim, const double *rr,
+                       const double *rr_s, int Vh, const int *active, int nact, hipStream_t s);
+// hout (pinned host memory, may be null): receives the sum too.
 hipError_t blas_finalize(const double *partial, int pstride, int nw, const int *active, int nact,
-                         int mode, double *rr, double *alpha, double *beta, double *out,
+                         int mode, double *rr, double *alpha, double *beta, double *out, double *hout,
                          hipStream_t s);
 // Reductions are formed from partial sums over groups of 16 consecutive sites.
 inline int ngroups_of(int nsites) { return (nsites + 15) / 16; }
@@ -256,8 +272,8 @@ struct wd_ctx {
 
     // named, growable device workspaces
     std::map<std::string, std::pair<void *, size_t>> ws;
-    void *pinned[2] = {nullptr, nullptr};   // [0] uploads, [1] downloads
-    size_t pinned_bytes[2] = {0, 0};
+    void *pinned[3] = {nullptr, nullptr, nullptr};  // [0] uploads, [1] downloads, [2] the one-shot solver's results
+    size_t pinned_bytes[3] = {0, 0, 0};
 
     // stencil timing
     bool timing = false;
@@ -300,6 +316,7 @@ struct Sweep {
     int P = 0;
     const char *links = nullptr;  // another copy of the packed links (else the context's)
     Field in, out, x, r;
+    const char *rsrc = nullptr;  // CG update: the field r is formed from, with r's strides (null: r)
     const double *coef = nullptr;
     const double *alpha = nullptr;
     const int *active = nullptr;

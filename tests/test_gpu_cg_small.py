@@ -4,7 +4,8 @@ the same bits and statistics: even-odd and full lattice, 18- and 12-real links,
 more right-hand sides than one launch takes, a residual check interval that
 does not divide the iteration cap, a starting guess, a zero and a non-finite
 source, and a session.  The largest lattices are at the limit of 256 sites of a
-vector; the last one is past it (both sides launch)."""
+vector; the last ones are past it, or have sites that do not fill
+groups of 16 (both sides launch)."""
 import numpy as np
 import pytest
 
@@ -30,7 +31,7 @@ def solve(wd, lat, B, kap, eo, graphs, x0=None, **kw):
 
 
 @pytest.mark.parametrize("eo,dims", [(1, (2, 2, 4, 4)), (1, (4, 4, 4, 4)), (1, (4, 4, 4, 8)), (0, (2, 4, 4, 4)), (0, (4, 4, 4, 4)),
-                                     (1, (6, 4, 4, 6))])
+                                     (1, (6, 4, 4, 6)), (0, (2, 2, 2, 2)), (0, (6, 2, 2, 6))])
 @pytest.mark.parametrize("recon", [18, 12])
 def test_one_launch_steps_equal_the_launches(wd, oracle, recon, eo, dims):
     V = li.volume(dims)
