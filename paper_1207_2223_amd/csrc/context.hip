@@ -112,42 +112,59 @@ TuneCfg default_cfg()
 
 // The launch shape of a sweep that has no tuned one (every shape gives the
 // same bits).  Lines drawn from the tuner's timings of all shapes; figures are
-// us a sweep, FP16 spinors unless said otherwise.
+// us a sweep (plain / xpay / CG update), sites x RHS in brackets.
 static TuneCfg untuned_cfg(const wd_ctx *c, const Sweep &sw)
 {
     TuneCfg t = default_cfg();
     const long long work = c->Vh * sw.nact;
-    // one wavefront a work-group: 16^3 x 32 with one RHS 8.4 -> 7.8 (plain), 10.1
-    // -> 9.2 (CG update); with 8 RHS 27.5 -> 24.7; FP64 8^3 x 16 6.7 -> 6.0
+    // one wavefront a work-group: FP16 16^3 x 32 with one RHS 7.7 / 8.7 / 9.1 ->
+    // 6.4 / 7.5 / 7.9, 12^3 x 24 with 5 7.5 / 9.2 / 9.6 -> 7.5 / 8.9 / 9.2
     t.block = 64;
-    // links of one RHS that exceed the last-level cache have no reuse: 32^3 x 64
-    // 102 -> 89 us, FP64 322 -> 306 (the same line as op_sweep's)
+    // links of one RHS that exceed the last-level cache have no reuse: FP16 32^3
+    // x 64 94 / 104 / 109 -> 88 / 97 / 102 (the same line as op_sweep's)
     if (sw.nact == 1 && (double)c->Vh * 8.0 * (double)link_bytes(sw.lk) > 180e6 && lnt_ok(sw.sp, sw.lk, t)) t.lnt = 1;
+    // fields of a batch beyond the caches: more RHS a lane read the links less
+    const bool large = work >= 1500000;
     if (sw.sp != SP_F64) {
-        // two RHS a lane share the link and its rebuilt row; with the
-        // epilogue's operands that pays once the chip is full (16^3 x 32, 8
-        // RHS: xpay 32.0 -> 29.5, CG update 35.3 -> 32.0; 24^3 x 48 151 -> 144,
-        // 169 -> 160), below it the lanes are missed (12^3 x 24, 5 RHS: 9.3 ->
-        // 10.0), and plain sweeps gain nothing (24^3 x 24, 6 RHS: 46.9 -> 49.2)
-        if (sw.epi != EPI_PLAIN && sw.nact >= 4 && work >= 250000 && dslash_shape_supported(sw.sp, sw.lk, 2, 1)) t.nr = 2;
+        if (sw.nact < 4 || work < 250000) return t;
+        // a t slab per XCD: FP16 32^4, 12 RHS [6.3 M], two a lane 315 / 367 / 416
+        // -> 281 / 329 / 368; 16^4, 12 RHS [393 k] 18.7 / 22.1 / 24.1 both ways;
+        // FP32 16^4, 12 RHS 28.1 / 36.3 / 41.0 -> 25.3 / 34.0 / 39.1
+        if (slab_order_ok(c->g, 64, 6)) t.remap = 6;
+        // FP16: two RHS a lane share the link and its rebuilt row once the chip
+        // is full (24^3 x 48, 8 RHS: 125 / 150 / 168 -> 114 / 136 / 151; 16^4, 12:
+        // 18.5 / 23.9 / 26.2 -> 18.7 / 22.1 / 24.1; 12^3 x 24, 5 RHS [104 k]: 7.5 /
+        // 8.9 / 9.2 -> 9.0 / 10.9 / 10.7); three in slabs where they divide the
+        // batch (32^4, 12 RHS: 281 / 329 / 368 -> 259 / 308 / 350, 16^4: none).
+        // FP32, whose terms take more registers, only beyond the caches (32^4,
+        // 4 RHS: 177 / 204 / 234 -> 167 / 190 / 222; 16^4, 12: 25.3 -> 26.3)
+        int nr = has_norm(sw.sp) || large ? 2 : 1;
+        if (has_norm(sw.sp) && large && t.remap == 6 && sw.nact % 3 == 0) nr = 3;
+        while (!dslash_shape_supported(sw.sp, sw.lk, nr, 1)) nr--;
+        t.nr = nr;
         return t;
     }
     if (sw.nact < 2 || work < 100000) return t;
-    if (slab_order_ok(c->g, 64, 6)) {
-        // a t slab per XCD, few sites in flight: 16^3 x 32, 8 RHS: plain 85.7
-        // -> 65.6 at 2 work-groups of 128 a CU, xpay 109 -> 90 with two lanes a
-        // site; 16^4, 12 RHS: 62.7 -> 51.1, 83.2 -> 71.3
-        const bool plain = sw.epi == EPI_PLAIN, b128 = slab_order_ok(c->g, plain ? 128 : 64, 6);
+    if (large && slab_order_ok(c->g, 64, 2)) {
+        // 32^4, 4 RHS [2.1 M]: 435 / 498 / 566 -> 333 / 389 / 437 (t slabs, one
+        // RHS a lane: 392 / 435 / 487); 16^3 x 32, 5 RHS [328 k]: 53 / 66 / 76
+        // against 42 / 54 / 60 by the next rule
+        t.remap = 2;
+        t.nr = 2;
+    } else if (slab_order_ok(c->g, 64, 6)) {
+        // a t slab per XCD, one wavefront a SIMD so that few sites are in
+        // flight: 16^3 x 32, 5 RHS: 51.2 / 62.8 / 71.5 -> 42.1 / 53.9 / 60
         t.remap = 6;
-        t.rl = plain ? 1 : 2;
-        t.block = b128 ? 128 : 64;
-        t.occ = !plain ? 0 : (b128 ? 2 : 4);
+        t.occ = 4;
     } else if (slab_order_ok(c->g, 32, 2)) {
-        // a z slab per XCD: 24^3 x 48, 8 RHS: 495 -> 440, 587 -> 504
+        // a z slab per XCD: 24^4, 6 RHS 182 / 200 / 224 -> 175 / 195 / 216; two RHS a
+        // lane where that leaves no slot empty: 24^3 x 48, 8 RHS 453 / 504 / 563
+        // -> 431 / 498 / 552 (24^4, 6 RHS: 197 / 231 / 257)
         t.remap = 2;
         t.rl = 2;
-    } else {
-        t.nr = 2;  // 12^3 x 24, 5 RHS: 18.1 -> 16.2, 23.6 -> 21.2
+        if (sw.nact % 4 == 0) t.nr = 2;
+    } else if (large) {
+        t.nr = 2;  // 24^3 x 48, 8 RHS: 514 / 577 / 659 -> 452 / 535 / 627
     }
     return t;
 }

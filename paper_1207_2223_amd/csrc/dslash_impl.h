@@ -216,109 +216,215 @@ struct LdsNb {
     }
 };
 
-// FP16 spinors with FP16 links: dot2 matvec on FP16 inputs, FP32 results.
-template <int MU, int NR, bool DAG, class NB>
-__device__ __forceinline__ void hop_dir_f16dot(const DslashArgs &a, const NB &nb, int i, const int c[4],
-                                               const int rid[NR], float acc[NR][24])
+// The terms of direction MU and sense DIR (+1: U psi(x + mu), -1: U^dag psi(x -
+// mu)) for the NR RHS of a lane, from the link as stored; nb supplies the
+// neighbour spinors.  FP16 spinors with FP16 links: dot2 matvec on FP16
+// inputs, FP32 results.
+template <int MU, int DIR, int SP, int LK, int NR, bool DAG, class NB, typename real>
+__device__ __forceinline__ void hop_apply(const DslashArgs &a, const NB &nb, const typename LinkIO<LK>::Raw &raw,
+                                          const int rid[NR], int j, real acc[NR][24])
 {
-    constexpr int SF = DAG ? +1 : -1;
-    constexpr int SB = -SF;
-    const int cs = a.g.cs;
-    h2_t A[9], B[9];
-    {
-        const int j = neighbour<MU, +1>(a.g, i, c);
-        link_forms_f16<false>(a.links, cs, a.P * 4 + MU, i, A, B);
+    constexpr int S = (DIR > 0) == DAG ? +1 : -1;  // forward: (1 - g) for H, (1 + g) for H^dag; backward: the opposite
+    if constexpr (SP == SP_F16 && LK == LK_F16_12) {
+        h2_t A[9], B[9];
+        link_forms_f16<(DIR < 0)>(raw, A, B);
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             h2_t v[12], h[6];
             float w[12];
-            const float sc = nb.template h2<MU, +1>(a, rid[r], r, j, v);
-            project_h2<MU, SF>(v, h);
+            const float sc = nb.template h2<MU, DIR>(a, rid[r], r, j, v);
+            project_h2<MU, S>(v, h);
             su3_mul_half_dot2(A, B, h, w);
-            accumulate_scaled<MU, SF>(acc[r], w, sc);
+            accumulate_scaled<MU, S>(acc[r], w, sc);
         }
-    }
-    {
-        const int j = neighbour<MU, -1>(a.g, i, c);
-        link_forms_f16<true>(a.links, cs, (1 - a.P) * 4 + MU, j, A, B);
+    } else {
+        real u[18];
+        LinkIO<LK>::expand(raw, u);
 #pragma unroll
         for (int r = 0; r < NR; r++) {
-            h2_t v[12], h[6];
-            float w[12];
-            const float sc = nb.template h2<MU, -1>(a, rid[r], r, j, v);
-            project_h2<MU, SB>(v, h);
-            su3_mul_half_dot2(A, B, h, w);
-            accumulate_scaled<MU, SB>(acc[r], w, sc);
+            real h[12], w[12], sc;
+            if constexpr (SP == SP_F16) {
+                _Float16 v[24];
+                sc = nb.template half<MU, DIR>(a, rid[r], r, j, v);
+                project_mix<MU, S>(v, h);
+            } else if constexpr (SP == SP_I16) {
+                int v[24];
+                sc = nb.template i16<MU, DIR>(a, rid[r], r, j, v);
+                project_int<MU, S>(v, h);
+            } else {
+                real v[24];
+                sc = nb.template gen<MU, DIR, SP>(a, rid[r], r, j, v);
+                project<MU, S>(v, h);
+            }
+            su3_mul_half<(DIR < 0)>(u, h, w);
+            if constexpr (has_norm(SP))
+                accumulate_scaled<MU, S>(acc[r], w, sc);
+            else
+                accumulate<MU, S>(acc[r], w);
         }
     }
 }
 
-// The two terms of direction MU for the NR RHS of a lane; nb supplies the
-// neighbour spinors.
+// The stored link of a term: the one at output site i, or at the neighbour j.
+template <int MU, int DIR, int LK>
+__device__ __forceinline__ void fetch_link(const DslashArgs &a, int i, int j, typename LinkIO<LK>::Raw &raw)
+{
+    LinkIO<LK>::fetch(a.links, a.g.cs, (DIR > 0 ? a.P : 1 - a.P) * 4 + MU, DIR > 0 ? i : j, raw);
+}
+
+// The two terms of direction MU for the NR RHS of a lane.
 template <int MU, int SP, int LK, int NR, bool DAG, class NB, typename real>
 __device__ __forceinline__ void hop_dir(const DslashArgs &a, const NB &nb, int i, const int c[4],
                                         const int rid[NR], real acc[NR][24])
 {
-    if constexpr (SP == SP_F16 && LK == LK_F16_12) {
-        hop_dir_f16dot<MU, NR, DAG>(a, nb, i, c, rid, acc);
-        return;
-    }
-    constexpr int SF = DAG ? +1 : -1;  // forward: (1 - g) for H, (1 + g) for H^dag
-    constexpr int SB = -SF;            // backward: the opposite projector
-    const int cs = a.g.cs;
-    real u[18];
+    typename LinkIO<LK>::Raw raw;
     {
         const int j = neighbour<MU, +1>(a.g, i, c);
-        LinkIO<LK>::load(a.links, cs, a.P * 4 + MU, i, u);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            real h[12], w[12], sc;
-            if constexpr (SP == SP_F16) {
-                _Float16 v[24];
-                sc = nb.template half<MU, +1>(a, rid[r], r, j, v);
-                project_mix<MU, SF>(v, h);
-            } else if constexpr (SP == SP_I16) {
-                int v[24];
-                sc = nb.template i16<MU, +1>(a, rid[r], r, j, v);
-                project_int<MU, SF>(v, h);
-            } else {
-                real v[24];
-                sc = nb.template gen<MU, +1, SP>(a, rid[r], r, j, v);
-                project<MU, SF>(v, h);
-            }
-            su3_mul_half<false>(u, h, w);
-            if constexpr (has_norm(SP))
-                accumulate_scaled<MU, SF>(acc[r], w, sc);
-            else
-                accumulate<MU, SF>(acc[r], w);
-        }
+        fetch_link<MU, +1, LK>(a, i, j, raw);
+        hop_apply<MU, +1, SP, LK, NR, DAG>(a, nb, raw, rid, j, acc);
     }
     {
         const int j = neighbour<MU, -1>(a.g, i, c);
-        LinkIO<LK>::load(a.links, cs, (1 - a.P) * 4 + MU, j, u);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            real h[12], w[12], sc;
-            if constexpr (SP == SP_F16) {
-                _Float16 v[24];
-                sc = nb.template half<MU, -1>(a, rid[r], r, j, v);
-                project_mix<MU, SB>(v, h);
-            } else if constexpr (SP == SP_I16) {
-                int v[24];
-                sc = nb.template i16<MU, -1>(a, rid[r], r, j, v);
-                project_int<MU, SB>(v, h);
-            } else {
-                real v[24];
-                sc = nb.template gen<MU, -1, SP>(a, rid[r], r, j, v);
-                project<MU, SB>(v, h);
-            }
-            su3_mul_half<true>(u, h, w);
-            if constexpr (has_norm(SP))
-                accumulate_scaled<MU, SB>(acc[r], w, sc);
-            else
-                accumulate<MU, SB>(acc[r], w);
-        }
+        fetch_link<MU, -1, LK>(a, i, j, raw);
+        hop_apply<MU, -1, SP, LK, NR, DAG>(a, nb, raw, rid, j, acc);
     }
+}
+
+// ---------------------------------------------------------------------------
+// Terms fetched ahead of their use
+// ---------------------------------------------------------------------------
+// Left to itself the compiler keeps one term and part of the next in flight
+// (74 registers for FP16 spinors) and a wavefront waits for memory about ten
+// times, which neither the few wavefronts of a small lattice nor the latency
+// of a large one's HBM reads hides.  dslash_kernel fetches the links and
+// spinors of a fixed number of terms, as stored, before it computes the
+// first, and refills each as it is used up.
+
+// A spinor as stored.
+template <int SP> struct SpinorRaw;
+template <> struct SpinorRaw<SP_F64> { dbl2_t ch[12]; };
+template <> struct SpinorRaw<SP_F32> { flt4_t ch[6]; };
+template <> struct SpinorRaw<SP_F16> {
+    half8_t ch[3];
+    float n;
+};
+template <> struct SpinorRaw<SP_I16> {
+    short8_t ch[3];
+    float n;
+};
+
+template <int SP, bool UNI>
+__device__ __forceinline__ void fetch_spinor(const char *f, int cs, int j, SpinorRaw<SP> &R)
+{
+    constexpr int n = sizeof(R.ch) / 16;
+    typedef std::remove_reference_t<decltype(R.ch[0])> T;
+    if constexpr (SP == SP_F64) {
+        const T *p = reinterpret_cast<const T *>(f) + j;
+#pragma unroll
+        for (int k = 0; k < n; k++) R.ch[k] = p[(size_t)k * cs];
+    } else {
+        const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
+#pragma unroll
+        for (int k = 0; k < n; k++) R.ch[k] = ld_off<T, UNI>(f + (size_t)k * cs * 16, off);
+    }
+    if constexpr (has_norm(SP))
+        R.n = ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u);
+}
+
+// What a term reads.
+template <int SP, int LK, int NR>
+struct TermRaw {
+    typename LinkIO<LK>::Raw u;
+    SpinorRaw<SP> s[NR];
+};
+
+// Neighbour source: the spinors of one term, in registers.
+template <int SP, int NR>
+struct RawNb {
+    const SpinorRaw<SP> (&s)[NR];
+    template <int MU, int DIR>
+    __device__ __forceinline__ float half(const DslashArgs &, int, int r, int, _Float16 v[24]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 24; k++) v[k] = s[r].ch[k / 8][k % 8];
+        return s[r].n;
+    }
+    template <int MU, int DIR>
+    __device__ __forceinline__ float h2(const DslashArgs &, int, int r, int, h2_t v[12]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 12; k++) v[k] = h2_t{s[r].ch[k / 4][2 * (k % 4)], s[r].ch[k / 4][2 * (k % 4) + 1]};
+        return s[r].n;
+    }
+    template <int MU, int DIR>
+    __device__ __forceinline__ float i16(const DslashArgs &, int, int r, int, int v[24]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 24; k++) v[k] = s[r].ch[k / 8][k % 8];
+        return SpinorIO<SP_I16>::step(s[r].n);
+    }
+    template <int MU, int DIR, int SP_, typename real>
+    __device__ __forceinline__ real gen(const DslashArgs &, int, int r, int, real v[24]) const
+    {
+        constexpr int e = 24 / (sizeof(s[0].ch) / 16);
+#pragma unroll
+        for (int k = 0; k < 24; k++) v[k] = s[r].ch[k / e][k % e];
+        return (real)1;
+    }
+};
+
+template <int K, int SP, int LK, int NR, bool UNI>
+__device__ __forceinline__ void fetch_term(const DslashArgs &a, const int rid[NR], int i, const int c[4],
+                                           TermRaw<SP, LK, NR> &T)
+{
+    constexpr int MU = K / 2, DIR = K % 2 ? -1 : +1;
+    const int j = neighbour<MU, DIR>(a.g, i, c);
+    fetch_link<MU, DIR, LK>(a, i, j, T.u);
+#pragma unroll
+    for (int r = 0; r < NR; r++) fetch_spinor<SP, UNI>(a.in + rid[r] * a.in_rs, a.g.cs, j, T.s[r]);
+}
+template <int K, int D, int SP, int LK, int NR, bool UNI>
+__device__ __forceinline__ void fetch_first(const DslashArgs &a, const int rid[NR], int i, const int c[4],
+                                            TermRaw<SP, LK, NR> (&T)[D])
+{
+    if constexpr (K < D) {
+        fetch_term<K, SP, LK, NR, UNI>(a, rid, i, c, T[K]);
+        fetch_first<K + 1, D, SP, LK, NR, UNI>(a, rid, i, c, T);
+    }
+}
+
+// Terms K..7, in the order of hop_dir; before_last() runs before term 7.
+template <int K, int D, int SP, int LK, int NR, bool DAG, bool UNI, typename real, class F>
+__device__ __forceinline__ void hop_terms(const DslashArgs &a, const int rid[NR], int i, const int c[4],
+                                          TermRaw<SP, LK, NR> (&T)[D], real acc[NR][24], F &&before_last)
+{
+    if constexpr (K < 8) {
+        if constexpr (K == 7) before_last();
+        const RawNb<SP, NR> nb{T[K % D].s};
+        hop_apply<K / 2, (K % 2 ? -1 : +1), SP, LK, NR, DAG>(a, nb, T[K % D].u, rid, 0, acc);
+        if constexpr (K + D < 8) fetch_term<K + D, SP, LK, NR, UNI>(a, rid, i, c, T[K % D]);
+        // (the scheduler must not move later fetches or terms across)
+        if constexpr (K < 7) __builtin_amdgcn_sched_barrier(0);
+        hop_terms<K + 1, D, SP, LK, NR, DAG, UNI>(a, rid, i, c, T, acc, before_last);
+    }
+}
+
+// Terms in flight (of depths 1 to 4; times in us, depth 0 the compiler's own
+// order of the same loads).  FP16, one RHS a lane, 16^3 x 32: xpay 9.2 -> 8.9,
+// 7.6, 7.9, 8.3; two RHS, 8 of them: 32.8 -> 32.7, 31.6, 32.8, 33.8 (CG
+// update); three, 32^3 x 64 with 12: 759 -> 735, 722, 711, 800.  FP32, one RHS,
+// 16^3 x 32: 9.3 -> 9.1, 6.7, 6.8, 7.2, 24^3 x 48 with 4: 134 -> 134, 121, 116,
+// 115; two: 140 -> 140, 121, 116, 114.  FP64, one RHS, 16^4: 11.0 -> 11.0, 9.6,
+// 9.6 (16^3 x 32 with 8, t slabs: 89.7 -> 83, 79.8, 82.4); two, 24^3 x 48 with
+// 4: 305 -> 237, 236, 289 and 32^3 x 64 with 12: 2515 -> 2188, 2242, 2619.
+// More terms cost registers, that is wavefronts: 118 for FP16, 150 for FP32
+// and 230 to 250 for FP64 at one RHS.
+template <int SP, int NR>
+__host__ __device__ constexpr int terms_ahead()
+{
+    if (SP == SP_F64) return NR == 1 ? 2 : 1;
+    if (SP == SP_F32) return NR <= 2 ? 3 : 1;
+    return NR <= 2 ? 2 : (NR == 3 ? 3 : 1);
 }
 
 // Sum over the 16 sites of a site group for lanes of equal RHS slot
@@ -331,74 +437,90 @@ __device__ __forceinline__ double group16_sum(double v)
     return v;
 }
 
-// The epilogue of output site i (live: a site of this lattice) for the NR
-// RHS of a lane (rv: the slot holds an active RHS): plain store, xpay with
-// |out|^2, or the CG residual update with |r|^2; the norm partials of 16
-// consecutive sites are summed with the same pairing tree for every shape.
+// The epilogue's operands at output site i.
+template <int SP, int EPI, typename real>
+__device__ __forceinline__ void epi_load(const DslashArgs &a, int i, int rid, real x[24], real r[24])
+{
+    if (EPI != EPI_PLAIN) SpinorIO<SP>::template load<true>(a.x + rid * a.x_rs, a.g.cs, i, x);
+    if (EPI == EPI_CGUPD) SpinorIO<SP>::template load<true>(a.rsrc + rid * a.r_rs, a.g.cs, i, r);
+}
+
+// The epilogue of one RHS at output site i: plain store, xpay with |out|^2, or
+// the CG residual update with |r|^2, stored and summed where st holds; the
+// norm partials of 16 consecutive sites are summed with the same pairing tree
+// for every shape.
+template <int SP, int RL, int EPI, typename real>
+__device__ __forceinline__ void epi_finish(const DslashArgs &a, int i, bool st, int rid, real acc[24], real x[24],
+                                           real r[24])
+{
+    const int cs = a.g.cs;
+    if (EPI == EPI_PLAIN) {
+        if (st) SpinorIO<SP>::template store<true>(a.out + rid * a.out_rs, cs, i, acc);
+        return;
+    }
+    double nrm = 0.0;
+    const real cf = (real)a.coef[rid];
+    if (EPI == EPI_XPAY) {
+#pragma unroll
+        for (int k = 0; k < 24; k++) {
+            x[k] = fmaT(cf, acc[k], x[k]);
+            nrm = fmaT((double)x[k], (double)x[k], nrm);
+        }
+        if (st) SpinorIO<SP>::template store<true>(a.out + rid * a.out_rs, cs, i, x);
+    } else {
+        const real al = a.alpha ? (real)a.alpha[rid] : (real)1;
+#pragma unroll
+        for (int k = 0; k < 24; k++) {
+            x[k] = fmaT(cf, acc[k], x[k]);
+            r[k] = fmaT(-al, x[k], r[k]);
+            nrm = fmaT((double)r[k], (double)r[k], nrm);
+        }
+        if (st) SpinorIO<SP>::template store<true>(a.r + rid * a.r_rs, cs, i, r);
+    }
+    if (a.partial != nullptr) {
+        const double s = group16_sum<RL>(st ? nrm : 0.0);
+        if (st && (i & 15) == 0 && ((int)threadIdx.x % (16 * RL)) < RL)
+            a.partial[(size_t)rid * a.pstride + a.pw_off + (i >> 4)] = s;
+    }
+}
+
+// The same for the NR RHS of a lane (live: i is a site of this lattice, rv:
+// the slot holds an active RHS).
 template <int SP, int NR, int RL, int EPI, typename real>
 __device__ __forceinline__ void dslash_epilogue(const DslashArgs &a, int i, bool live, const int (&rid)[NR],
                                                 const bool (&rv)[NR], real (&acc)[NR][24])
 {
-    const int Vh = a.g.Vh, cs = a.g.cs;
 #pragma unroll
     for (int r = 0; r < NR; r++) {
-        double nrm = 0.0;
-        if (live && rv[r]) {
-            if (EPI == EPI_PLAIN) {
-                SpinorIO<SP>::template store<true>(a.out + rid[r] * a.out_rs, cs, i, acc[r]);
-            } else if (EPI == EPI_XPAY) {
-                const real cf = (real)a.coef[rid[r]];
-                real xv[24];
-                SpinorIO<SP>::template load<true>(a.x + rid[r] * a.x_rs, cs, i, xv);
-#pragma unroll
-                for (int k = 0; k < 24; k++) {
-                    xv[k] = fmaT(cf, acc[r][k], xv[k]);
-                    nrm = fmaT((double)xv[k], (double)xv[k], nrm);
-                }
-                SpinorIO<SP>::template store<true>(a.out + rid[r] * a.out_rs, cs, i, xv);
-            } else {
-                const real cf = (real)a.coef[rid[r]];
-                const real al = a.alpha ? (real)a.alpha[rid[r]] : (real)1;
-                real ap[24], rv_[24];
-                SpinorIO<SP>::template load<true>(a.x + rid[r] * a.x_rs, cs, i, ap);
-                SpinorIO<SP>::template load<true>(a.rsrc + rid[r] * a.r_rs, cs, i, rv_);
-#pragma unroll
-                for (int k = 0; k < 24; k++) {
-                    ap[k] = fmaT(cf, acc[r][k], ap[k]);
-                    rv_[k] = fmaT(-al, ap[k], rv_[k]);
-                    nrm = fmaT((double)rv_[k], (double)rv_[k], nrm);
-                }
-                SpinorIO<SP>::template store<true>(a.r + rid[r] * a.r_rs, cs, i, rv_);
-            }
-        }
-        if (EPI != EPI_PLAIN && a.partial != nullptr) {
-            const double s = group16_sum<RL>(nrm);
-            if ((i & 15) == 0 && i < Vh && rv[r] && ((int)threadIdx.x % (16 * RL)) < RL)
-                a.partial[(size_t)rid[r] * a.pstride + a.pw_off + (i >> 4)] = s;
-        }
+        real x[24], rr[24];
+        epi_load<SP, EPI>(a, live ? i : a.g.Vh - 1, rid[r], x, rr);
+        epi_finish<SP, RL, EPI>(a, i, live && rv[r], rid[r], acc[r], x, rr);
     }
 }
 
-template <int SP, int LK, int NR, int RL, bool DAG, int EPI>
-__global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
+// The leading work-groups, if any, finalize the CG alpha of one active RHS
+// each (first wavefront; the order of every CG scalar's sum), the others are
+// the stencil's tiles; they are independent of each other.  True in the former.
+__device__ __forceinline__ bool finalize_blocks(const DslashArgs &a)
 {
-    typedef typename SpinorIO<SP>::real real;
-    static_assert(sizeof(typename LinkIO<LK>::real) == sizeof(real), "link/spinor precision pair");
-    // the leading work-groups, if any, finalize the CG alpha of one active
-    // RHS each (first wavefront; the order of every CG scalar's sum), the
-    // others are the stencil's tiles; they are independent of each other
     if ((int)blockIdx.x < a.fin_blocks) {
         if (threadIdx.x < 64) {
             const int rid = a.active[blockIdx.x];
             const double s = fin_wave_sum(a.fin_partial + (size_t)rid * a.fin_pstride, a.fin_nw, (int)threadIdx.x);
             if (threadIdx.x == 0) fin_alpha_update(s, rid, a.fin_rr, a.fin_alpha, a.fin_out);
         }
-        return;
+        return true;
     }
+    return false;
+}
+
+// The tile of sites and the RHS group of a stencil work-group, by the tile
+// order of the launch.
+__device__ __forceinline__ void tile_of_block(const DslashArgs &a, int &tile, int &grp)
+{
     // tile blocks: index and count without the finalize blocks (a block's
     // XCD is still its index mod 8, shifted alike for all of them)
     const int bid = (int)blockIdx.x - a.fin_blocks, nblk = (int)gridDim.x - a.fin_blocks;
-    int tile, grp;
     if (a.remap == 7) {
         // z-slab per XCD as order 2, but RHS-group-major: the XCD sweeps its
         // whole slab for one RHS group before the next, so only NR*RL RHS of
@@ -451,10 +573,24 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
         tile = L / a.G;
         grp = L - tile * a.G;
     }
+}
+
+template <int SP, int LK, int NR, int RL, bool DAG, int EPI>
+__global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
+{
+    typedef typename SpinorIO<SP>::real real;
+    static_assert(sizeof(typename LinkIO<LK>::real) == sizeof(real), "link/spinor precision pair");
+    if (finalize_blocks(a)) return;
+    int tile, grp;
+    tile_of_block(a, tile, grp);
+    constexpr bool UNI = RL == 1;
     const int spb = blockDim.x / RL;
-    const int i = tile * spb + (int)threadIdx.x / RL;
+    const int i0 = tile * spb + (int)threadIdx.x / RL;
     const int lr = (int)threadIdx.x % RL;
-    const bool live = i < a.g.Vh;
+    // lanes past the end compute the last site and store nothing: without a
+    // branch around the terms the epilogue's operands are fetched under them
+    const bool live = i0 < a.g.Vh;
+    const int i = live ? i0 : a.g.Vh - 1;
 
     int rid[NR];
     bool rv[NR];
@@ -468,26 +604,34 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
         // with one lane per site the slot depends on the block only, so the
         // RHS id is the same in every lane: keep it (and the field bases
         // derived from it) in scalar registers
-        if constexpr (RL == 1) rid[r] = __builtin_amdgcn_readfirstlane(rid[r]);
+        if constexpr (UNI) rid[r] = __builtin_amdgcn_readfirstlane(rid[r]);
     }
 
+    constexpr int D = terms_ahead<SP, NR>();
+    int c[4];
+    site_coords(a.g, i, a.P, c);
+    TermRaw<SP, LK, NR> T[D];
+    fetch_first<0, D, SP, LK, NR, UNI>(a, rid, i, c, T);
+    __builtin_amdgcn_sched_barrier(0);
     real acc[NR][24];
 #pragma unroll
     for (int r = 0; r < NR; r++)
 #pragma unroll
         for (int k = 0; k < 24; k++) acc[r][k] = 0;
-
-    if (live) {
-        int c[4];
-        site_coords(a.g, i, a.P, c);
-        const GlobalNb<RL == 1> nb;
-        hop_dir<0, SP, LK, NR, DAG>(a, nb, i, c, rid, acc);
-        hop_dir<1, SP, LK, NR, DAG>(a, nb, i, c, rid, acc);
-        hop_dir<2, SP, LK, NR, DAG>(a, nb, i, c, rid, acc);
-        hop_dir<3, SP, LK, NR, DAG>(a, nb, i, c, rid, acc);
-    }
-
-    dslash_epilogue<SP, NR, RL, EPI>(a, i, live, rid, rv, acc);
+    real x[24], rr[24];
+    hop_terms<0, D, SP, LK, NR, DAG, UNI>(a, rid, i, c, T, acc, [&] {
+        if constexpr (NR == 1) epi_load<SP, EPI>(a, i, rid[0], x, rr);
+    });
+    // (opaque: the terms must not be moved into the branch of the stores, past
+    // the barriers above)
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+#pragma unroll
+        for (int k = 0; k < 24; k++) asm volatile("" : "+v"(acc[r][k]));
+    if constexpr (NR == 1)
+        epi_finish<SP, RL, EPI>(a, i, live && rv[0], rid[0], acc[0], x, rr);
+    else
+        dslash_epilogue<SP, NR, RL, EPI>(a, i, live, rid, rv, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -582,14 +726,7 @@ __global__ void __launch_bounds__(kLdsThreads) dslash_lds_kernel(DslashArgs a)
     static_assert(SP == SP_F16 || SP == SP_F32, "LDS staging of FP16 and FP32 spinors");
     constexpr int SPT = kLdsMaxPlane / kLdsThreads;  // sites per thread and plane, at most
     extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
-    if ((int)blockIdx.x < a.fin_blocks) {
-        if (threadIdx.x < 64) {
-            const int rid = a.active[blockIdx.x];
-            const double s = fin_wave_sum(a.fin_partial + (size_t)rid * a.fin_pstride, a.fin_nw, (int)threadIdx.x);
-            if (threadIdx.x == 0) fin_alpha_update(s, rid, a.fin_rr, a.fin_alpha, a.fin_out);
-        }
-        return;
-    }
+    if (finalize_blocks(a)) return;
     const int bid = (int)blockIdx.x - a.fin_blocks;
     const int Lz = a.g.L[2], Lt = a.g.L[3];
     const int S = a.g.Lxh * a.g.L[1];
@@ -753,14 +890,7 @@ template <int SP, int LK, int NR, bool DAG, int EPI>
 __global__ void __launch_bounds__(256) dslash_tw_kernel(DslashArgs a)
 {
     static_assert(SP == SP_F16, "t-walking stencil: FP16 spinors");
-    if ((int)blockIdx.x < a.fin_blocks) {
-        if (threadIdx.x < 64) {
-            const int rid = a.active[blockIdx.x];
-            const double s = fin_wave_sum(a.fin_partial + (size_t)rid * a.fin_pstride, a.fin_nw, (int)threadIdx.x);
-            if (threadIdx.x == 0) fin_alpha_update(s, rid, a.fin_rr, a.fin_alpha, a.fin_out);
-        }
-        return;
-    }
+    if (finalize_blocks(a)) return;
     const int bid = (int)blockIdx.x - a.fin_blocks;
     const int Lz = a.g.L[2], Lt = a.g.L[3];
     const int S = a.g.Lxh * a.g.L[1];

@@ -397,64 +397,71 @@ __device__ __forceinline__ void reconstruct_row3(T u[18])
 
 template <int LK> struct LinkIO;
 
-template <bool NT>
-struct LinkIOF64x18 {
+// (fetch: the words as stored; expand: all nine entries from them)
+template <bool NT, int N>
+struct LinkIOF64 {
     typedef double real;
-    static constexpr int nchunk = 9;
+    static constexpr int nchunk = N / 2;
     static constexpr size_t chunk_bytes = 16;
+    struct Raw { dbl2_t w[N / 2]; };
+    __device__ static __forceinline__ void fetch(const char *U, int cs, int blk, int i, Raw &r)
+    {
+        const dbl2_t *p = reinterpret_cast<const dbl2_t *>(U) + (size_t)blk * (N / 2) * cs;
+#pragma unroll
+        for (int k = 0; k < N / 2; k++) r.w[k] = ld_hint<NT>(p + (size_t)k * cs + i);
+    }
+    __device__ static __forceinline__ void expand(const Raw &r, double u[18])
+    {
+#pragma unroll
+        for (int k = 0; k < N / 2; k++) {
+            u[2 * k] = r.w[k].x;
+            u[2 * k + 1] = r.w[k].y;
+        }
+        if constexpr (N == 12) reconstruct_row3(u);
+    }
     __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, double u[18])
     {
-        const dbl2_t *p = reinterpret_cast<const dbl2_t *>(U) + (size_t)blk * 9 * cs;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const dbl2_t w = ld_hint<NT>(p + (size_t)k * cs + i);
-            u[2 * k] = w.x;
-            u[2 * k + 1] = w.y;
-        }
+        Raw r;
+        fetch(U, cs, blk, i, r);
+        expand(r, u);
     }
 };
-template <> struct LinkIO<LK_F64_18> : LinkIOF64x18<false> {};
-template <> struct LinkIO<LK_F64_18N> : LinkIOF64x18<true> {};
-
-template <bool NT>
-struct LinkIOF64x12 {
-    typedef double real;
-    static constexpr int nchunk = 6;
-    static constexpr size_t chunk_bytes = 16;
-    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, double u[18])
-    {
-        const dbl2_t *p = reinterpret_cast<const dbl2_t *>(U) + (size_t)blk * 6 * cs;
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            const dbl2_t w = ld_hint<NT>(p + (size_t)k * cs + i);
-            u[2 * k] = w.x;
-            u[2 * k + 1] = w.y;
-        }
-        reconstruct_row3(u);
-    }
-};
-template <> struct LinkIO<LK_F64_12> : LinkIOF64x12<false> {};
-template <> struct LinkIO<LK_F64_12N> : LinkIOF64x12<true> {};
+template <> struct LinkIO<LK_F64_18> : LinkIOF64<false, 18> {};
+template <> struct LinkIO<LK_F64_18N> : LinkIOF64<true, 18> {};
+template <> struct LinkIO<LK_F64_12> : LinkIOF64<false, 12> {};
+template <> struct LinkIO<LK_F64_12N> : LinkIOF64<true, 12> {};
 
 template <bool NT>
 struct LinkIOF32x12 {
     typedef float real;
     static constexpr int nchunk = 3;
     static constexpr size_t chunk_bytes = 16;
-    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
+    struct Raw { flt4_t w[3]; };
+    __device__ static __forceinline__ void fetch(const char *U, int cs, int blk, int i, Raw &r)
     {
         const char *p = U + (size_t)blk * 3 * cs * 16;
         const uint32_t off = (uint32_t)i * 16u;
 #pragma unroll
+        for (int k = 0; k < 3; k++)
+            r.w[k] = NT ? ld_off_nt<flt4_t, true>(p + (size_t)k * cs * 16, off)
+                        : ld_off<flt4_t, true>(p + (size_t)k * cs * 16, off);
+    }
+    __device__ static __forceinline__ void expand(const Raw &r, float u[18])
+    {
+#pragma unroll
         for (int k = 0; k < 3; k++) {
-            const flt4_t w = NT ? ld_off_nt<flt4_t, true>(p + (size_t)k * cs * 16, off)
-                                : ld_off<flt4_t, true>(p + (size_t)k * cs * 16, off);
-            u[4 * k] = w.x;
-            u[4 * k + 1] = w.y;
-            u[4 * k + 2] = w.z;
-            u[4 * k + 3] = w.w;
+            u[4 * k] = r.w[k].x;
+            u[4 * k + 1] = r.w[k].y;
+            u[4 * k + 2] = r.w[k].z;
+            u[4 * k + 3] = r.w[k].w;
         }
         reconstruct_row3(u);
+    }
+    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
+    {
+        Raw r;
+        fetch(U, cs, blk, i, r);
+        expand(r, u);
     }
 };
 template <> struct LinkIO<LK_F32_12> : LinkIOF32x12<false> {};
@@ -467,16 +474,25 @@ template <> struct LinkIO<LK_F16_12> {
     typedef float real;
     static constexpr int nchunk = 3;
     static constexpr size_t chunk_bytes = 8;
+    struct Raw { half4_t w[3]; };
+    __device__ static __forceinline__ void fetch(const char *U, int cs, int blk, int i, Raw &r)
+    {
+        const char *p = U + (size_t)blk * 3 * cs * 8;
+        const uint32_t off = (uint32_t)i * 8u;
+#pragma unroll
+        for (int k = 0; k < 3; k++) r.w[k] = ld_off<half4_t, true>(p + (size_t)k * cs * 8, off);
+    }
+    __device__ static __forceinline__ void expand(const Raw &r, float u[18])
+    {
+#pragma unroll
+        for (int k = 0; k < 12; k++) u[k] = (float)r.w[k / 4][k % 4];
+        reconstruct_row3(u);
+    }
     __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
     {
-        const half4_t *p = reinterpret_cast<const half4_t *>(U) + (size_t)blk * 3 * cs;
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            half4_t w = p[(size_t)k * cs + i];
-#pragma unroll
-            for (int j = 0; j < 4; j++) u[4 * k + j] = (float)w[j];
-        }
-        reconstruct_row3(u);
+        Raw r;
+        fetch(U, cs, blk, i, r);
+        expand(r, u);
     }
 };
 
@@ -485,22 +501,36 @@ template <> struct LinkIO<LK_F16_12> {
 // second region after all eight float4 blocks.
 template <> struct LinkIO<LK_F32_18> {
     typedef float real;
-    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
+    struct Raw {
+        float4 w[4];
+        float2 e;
+    };
+    __device__ static __forceinline__ void fetch(const char *U, int cs, int blk, int i, Raw &r)
     {
         const float4 *p = reinterpret_cast<const float4 *>(U) + (size_t)blk * 4 * cs;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            float4 w = p[(size_t)k * cs + i];
-            u[4 * k] = w.x;
-            u[4 * k + 1] = w.y;
-            u[4 * k + 2] = w.z;
-            u[4 * k + 3] = w.w;
-        }
+        for (int k = 0; k < 4; k++) r.w[k] = p[(size_t)k * cs + i];
         const float2 *q = reinterpret_cast<const float2 *>(reinterpret_cast<const float4 *>(U) + (size_t)32 * cs) +
                           (size_t)blk * cs;
-        float2 w = q[i];
-        u[16] = w.x;
-        u[17] = w.y;
+        r.e = q[i];
+    }
+    __device__ static __forceinline__ void expand(const Raw &r, float u[18])
+    {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            u[4 * k] = r.w[k].x;
+            u[4 * k + 1] = r.w[k].y;
+            u[4 * k + 2] = r.w[k].z;
+            u[4 * k + 3] = r.w[k].w;
+        }
+        u[16] = r.e.x;
+        u[17] = r.e.y;
+    }
+    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
+    {
+        Raw r;
+        fetch(U, cs, blk, i, r);
+        expand(r, u);
     }
 };
 
@@ -527,13 +557,25 @@ template <> struct LinkIO<LK_F32_18> {
 template <bool NT>
 struct LinkIOF32x8 {
     typedef float real;
-    __device__ static __forceinline__ void load(const char *U8, int cs, int blk, int i, float u[18])
+    struct Raw { flt4_t w[2]; };
+    __device__ static __forceinline__ void fetch(const char *U8, int cs, int blk, int i, Raw &r)
     {
         const char *p = U8 + (size_t)blk * 2 * cs * 16;
         const uint32_t off = (uint32_t)i * 16u;
-        const flt4_t w0 = NT ? ld_off_nt<flt4_t, true>(p, off) : ld_off<flt4_t, true>(p, off);
-        const flt4_t w1 = NT ? ld_off_nt<flt4_t, true>(p + (size_t)cs * 16, off)
-                            : ld_off<flt4_t, true>(p + (size_t)cs * 16, off);
+#pragma unroll
+        for (int k = 0; k < 2; k++)
+            r.w[k] = NT ? ld_off_nt<flt4_t, true>(p + (size_t)k * cs * 16, off)
+                        : ld_off<flt4_t, true>(p + (size_t)k * cs * 16, off);
+    }
+    __device__ static __forceinline__ void load(const char *U, int cs, int blk, int i, float u[18])
+    {
+        Raw r;
+        fetch(U, cs, blk, i, r);
+        expand(r, u);
+    }
+    __device__ static __forceinline__ void expand(const Raw &r, float u[18])
+    {
+        const flt4_t w0 = r.w[0], w1 = r.w[1];
         const float a2r = w0.x, a2i = w0.y, a3r = w0.z, a3i = w0.w, b1r = w1.x, b1i = w1.y;
         const int k = (int)(__float_as_uint(w1.z) & 3u);
         const unsigned cb = __float_as_uint(w1.w) & 3u;
@@ -850,20 +892,14 @@ typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 //   adjoint (conj u[b][a]):     re = A.h, A = (ur,  ui);  im = B.h, B = (-ui, ur)
 // indexed [3a + b] for output colour a, input colour b.
 template <bool ADJ>
-__device__ __forceinline__ void link_forms_f16(const char *U, int cs, int blk, int i, h2_t A[9], h2_t B[9])
+__device__ __forceinline__ void link_forms_f16(const LinkIO<LK_F16_12>::Raw &r, h2_t A[9], h2_t B[9])
 {
-    const char *p = U + (size_t)blk * 3 * cs * 8;
-    const uint32_t off = (uint32_t)i * 8u;
     float u[18];
     _Float16 hv[18];
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        const half4_t w = ld_off<half4_t, true>(p + (size_t)k * cs * 8, off);
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            hv[4 * k + j] = w[j];
-            u[4 * k + j] = (float)w[j];
-        }
+    for (int k = 0; k < 12; k++) {
+        hv[k] = r.w[k / 4][k % 4];
+        u[k] = (float)hv[k];
     }
     reconstruct_row3(u);
 #pragma unroll

@@ -14,8 +14,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dims,nrhs", [((16, 16, 16, 8), 7),    # t slabs, 128-site tiles
                                        ((8, 16, 18, 16), 6),    # t slabs, 64-site tiles
                                        ((16, 12, 16, 18), 4),   # z slabs, 32-site tiles
-                                       ((12, 12, 12, 12), 26),  # two RHS a lane
-                                       ((16, 16, 16, 16), 8)])  # FP16 xpay and CG update with two RHS a lane
+                                       ((12, 12, 12, 12), 26),  # no slabs
+                                       ((16, 16, 16, 16), 8),   # FP16 two RHS a lane in t slabs
+                                       ((16, 12, 16, 18), 5),   # z slabs, one RHS a lane
+                                       ((16, 16, 16, 16), 48)]) # large batches: two and three RHS a lane
 @pytest.mark.parametrize("prec", ["f64", "f16", "f32r8"])
 def test_batch_equals_single_solves(prec, dims, nrhs):
     from paper_1207_2223_amd import wd
