@@ -328,20 +328,21 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
 }
 
 // Whether the first sweep of a call reads the caller's field where it lies
-// (its neighbours at 192-byte strides) or a packed copy.  Small lattices are
-// launch-bound and save the pack; FP64 12-real sweeps keep winning (24^3 x 48
-// parity: 95 us against 109, 32^3 x 64: 292 against 338), the others lose
-// where the strided reads stop hitting the caches: FP64 18-real at 24^3 x 24
-// 63 against 70 us, at 24^3 x 48 146 against 135; FP32 at 16^3 x 32 16.0
-// against 18.2, at 24^3 x 24 47 against 34, FP16 alike.
-bool op_reads_canonical(const wd_ctx *c, int sp, int lk, int np, const void *in, const void *out, size_t in_bytes,
+// (its neighbours at 192-byte strides) or a packed copy.  FP64 reads it where
+// it lies at all sizes: D_eo, 18-real links, packed and here: 16^3 x 32 30.3 and
+// 20.0 us, 24^3 x 48 129 and 117, 32^3 x 64 399 and 364; both parities, 12-real:
+// 41.4 and 36.5, 216 and 223, 757 and 701.  The other formats, which encode
+// each neighbour eight times, only while the call is bound by its launches:
+// FP32 and FP16, one parity: 20^4 21.9 and 17.9, 20.2 and 18.8, 24^4 35.3 and
+// 35.8, 31.1 and 36.8; both: 12^3 x 24 13.4 and 11.8, 16^4 18.1 and 18.4, 16.1
+// and 18.5.
+bool op_reads_canonical(const wd_ctx *c, int sp, int np, const void *in, const void *out, size_t in_bytes,
                         size_t out_bytes)
 {
     // (the output must not overwrite neighbours that other lanes have yet to read)
     const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
     if (!(a + in_bytes <= b || b + out_bytes <= a)) return false;
-    const long long sites = c->Vh * np;
-    return lk == LK_F64_12 || sites <= (sp == SP_F64 ? 200000 : 65536);
+    return sp == SP_F64 || c->Vh <= (np == 2 ? 25000 : 100000);
 }
 
 wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs)
@@ -621,7 +622,7 @@ wd_status wd_dslash(wd_ctx *c, double *out, const double *in, int out_parity, in
     o.full = full;
     o.np = full ? 2 : 1;
     o.P0 = out_parity == WD_ODD ? 1 : 0;
-    if (op_reads_canonical(c, sp, lk, o.np, in, out, bytes, bytes)) {
+    if (op_reads_canonical(c, sp, o.np, in, out, bytes, bytes)) {
         o.incanon = 1;
         o.in = (const char *)in;
     } else {
@@ -708,22 +709,12 @@ wd_status wd_dslash_shaped(wd_ctx *c, double *out, const double *in, int nrhs, i
 extern "C++" {
 namespace wd {
 
-wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &A, const Field &T,
-                      const Field &B)
+wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &T, const Field &B)
 {
-    const size_t bytes = (size_t)(eo ? c->Vh : c->V) * 192;
     // (the last sweep writes out when nothing reads in any more)
-    const bool canon = op_reads_canonical(c, SP_F64, c->lk64, eo ? 1 : 2, in, nullptr, bytes, 0);
     OpArgs o;
-    if (canon) {
-        o.incanon = 1;
-        o.in = (const char *)in;
-    } else {
-        const hipError_t e = pack_spinor(in, A, 1, eo ? 0 : 1, c->g, c->stream);
-        if (e != hipSuccess) return set_error(WD_ERR_HIP, "pack: %s", hipGetErrorString(e));
-        o.in = A.base;
-        o.in_ss = eo ? 0 : A.ss;
-    }
+    o.incanon = 1;
+    o.in = (const char *)in;
     if (eo) {
         const OpArgs in_e = o;  // the operand on the even sites
         OpArgs s1 = in_e;       // T = D_oe in
@@ -734,7 +725,7 @@ wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, in
         s2.in = T.base;
         s2.xpay = 1;
         s2.coef = -kappa * kappa;
-        s2.xcanon = in_e.incanon;
+        s2.xcanon = 1;
         s2.x = in_e.in;
         s2.out = B.base;
         WD_TRY(op_sweep(c, s2, SP_F64, c->lk64, 0, 1));
@@ -757,9 +748,8 @@ wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, in
     o.xpay = 1;
     o.coef = -kappa;
     OpArgs m = o;  // T = M in
-    m.xcanon = o.incanon;
+    m.xcanon = 1;
     m.x = o.in;
-    m.x_ss = o.in_ss;
     m.out = T.base;
     m.out_ss = T.ss;
     WD_TRY(op_sweep(c, m, SP_F64, c->lk64, 0, 1));
@@ -784,11 +774,10 @@ wd_status wd_mdagm(wd_ctx *c, double *out, const double *in, double kappa, int e
     if (!std::isfinite(kappa)) return set_error(WD_ERR_ARG, "kappa not finite");
     WD_HIP(hipSetDevice(c->device));
     const int nsub = eo ? 1 : 2;
-    Field A, T, B;
-    WD_TRY(alloc_field(c, "mdm_a", SP_F64, nsub, 1, &A));
+    Field T, B;
     WD_TRY(alloc_field(c, "mdm_t", SP_F64, nsub, 1, &T));
     WD_TRY(alloc_field(c, "mdm_b", SP_F64, nsub, 1, &B));
-    return mdagm_apply(c, out, in, kappa, eo, A, T, B);
+    return mdagm_apply(c, out, in, kappa, eo, T, B);
 }
 
 wd_status wd_index_tables(const int32_t dims[4], int32_t *nb, int32_t *cb, uint8_t *par)

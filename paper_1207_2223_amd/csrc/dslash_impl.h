@@ -313,32 +313,7 @@ template <> struct SpinorRaw<SP_I16> {
     float n;
 };
 
-template <int SP, bool UNI>
-__device__ __forceinline__ void fetch_spinor(const char *f, int cs, int j, SpinorRaw<SP> &R)
-{
-    constexpr int n = sizeof(R.ch) / 16;
-    typedef std::remove_reference_t<decltype(R.ch[0])> T;
-    if constexpr (SP == SP_F64) {
-        const T *p = reinterpret_cast<const T *>(f) + j;
-#pragma unroll
-        for (int k = 0; k < n; k++) R.ch[k] = p[(size_t)k * cs];
-    } else {
-        const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
-#pragma unroll
-        for (int k = 0; k < n; k++) R.ch[k] = ld_off<T, UNI>(f + (size_t)k * cs * 16, off);
-    }
-    if constexpr (has_norm(SP))
-        R.n = ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u);
-}
-
-// What a term reads.
-template <int SP, int LK, int NR>
-struct TermRaw {
-    typename LinkIO<LK>::Raw u;
-    SpinorRaw<SP> s[NR];
-};
-
-// Neighbour source: the spinors of one term, in registers.
+// Neighbour source of a term: its NR spinors, in registers.
 template <int SP, int NR>
 struct RawNb {
     const SpinorRaw<SP> (&s)[NR];
@@ -373,40 +348,96 @@ struct RawNb {
     }
 };
 
-template <int K, int SP, int LK, int NR, bool UNI>
-__device__ __forceinline__ void fetch_term(const DslashArgs &a, const int rid[NR], int i, const int c[4],
-                                           TermRaw<SP, LK, NR> &T)
+// Where the terms' spinors are fetched from: the packed input field (UNI: its
+// base is the same in every lane).
+template <int SP, bool UNI>
+struct PackedSrc {
+    typedef SpinorRaw<SP> Raw;
+    template <int NR> using Nb = RawNb<SP, NR>;
+    template <int MU>
+    __device__ __forceinline__ void fetch(const DslashArgs &a, int rid, int j, Raw &R) const
+    {
+        const char *f = a.in + rid * a.in_rs;
+        const int cs = a.g.cs;
+        constexpr int n = sizeof(R.ch) / 16;
+        typedef std::remove_reference_t<decltype(R.ch[0])> T;
+        if constexpr (SP == SP_F64) {
+            const T *p = reinterpret_cast<const T *>(f) + j;
+#pragma unroll
+            for (int k = 0; k < n; k++) R.ch[k] = p[(size_t)k * cs];
+        } else {
+            const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
+#pragma unroll
+            for (int k = 0; k < n; k++) R.ch[k] = ld_off<T, UNI>(f + (size_t)k * cs * 16, off);
+        }
+        if constexpr (has_norm(SP))
+            R.n = ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u);
+    }
+};
+
+// What a term reads.
+template <class SRC, int LK, int NR>
+struct TermRaw {
+    typename LinkIO<LK>::Raw u;
+    typename SRC::Raw s[NR];
+};
+
+template <int K, int LK, int NR, class SRC>
+__device__ __forceinline__ void fetch_term(const DslashArgs &a, const SRC &src, const int rid[NR], int i,
+                                           const int c[4], TermRaw<SRC, LK, NR> &T)
 {
     constexpr int MU = K / 2, DIR = K % 2 ? -1 : +1;
     const int j = neighbour<MU, DIR>(a.g, i, c);
     fetch_link<MU, DIR, LK>(a, i, j, T.u);
 #pragma unroll
-    for (int r = 0; r < NR; r++) fetch_spinor<SP, UNI>(a.in + rid[r] * a.in_rs, a.g.cs, j, T.s[r]);
+    for (int r = 0; r < NR; r++) src.template fetch<MU>(a, rid[r], j, T.s[r]);
 }
-template <int K, int D, int SP, int LK, int NR, bool UNI>
-__device__ __forceinline__ void fetch_first(const DslashArgs &a, const int rid[NR], int i, const int c[4],
-                                            TermRaw<SP, LK, NR> (&T)[D])
+template <int K, int D, int LK, int NR, class SRC>
+__device__ __forceinline__ void fetch_first(const DslashArgs &a, const SRC &src, const int rid[NR], int i,
+                                            const int c[4], TermRaw<SRC, LK, NR> (&T)[D])
 {
     if constexpr (K < D) {
-        fetch_term<K, SP, LK, NR, UNI>(a, rid, i, c, T[K]);
-        fetch_first<K + 1, D, SP, LK, NR, UNI>(a, rid, i, c, T);
+        fetch_term<K, LK, NR>(a, src, rid, i, c, T[K]);
+        fetch_first<K + 1, D, LK, NR>(a, src, rid, i, c, T);
     }
 }
 
 // Terms K..7, in the order of hop_dir; before_last() runs before term 7.
-template <int K, int D, int SP, int LK, int NR, bool DAG, bool UNI, typename real, class F>
-__device__ __forceinline__ void hop_terms(const DslashArgs &a, const int rid[NR], int i, const int c[4],
-                                          TermRaw<SP, LK, NR> (&T)[D], real acc[NR][24], F &&before_last)
+template <int K, int D, int SP, int LK, int NR, bool DAG, class SRC, typename real, class F>
+__device__ __forceinline__ void hop_terms(const DslashArgs &a, const SRC &src, const int rid[NR], int i,
+                                          const int c[4], TermRaw<SRC, LK, NR> (&T)[D], real acc[NR][24],
+                                          F &&before_last)
 {
     if constexpr (K < 8) {
         if constexpr (K == 7) before_last();
-        const RawNb<SP, NR> nb{T[K % D].s};
+        const typename SRC::template Nb<NR> nb{T[K % D].s};
         hop_apply<K / 2, (K % 2 ? -1 : +1), SP, LK, NR, DAG>(a, nb, T[K % D].u, rid, 0, acc);
-        if constexpr (K + D < 8) fetch_term<K + D, SP, LK, NR, UNI>(a, rid, i, c, T[K % D]);
+        if constexpr (K + D < 8) fetch_term<K + D, LK, NR>(a, src, rid, i, c, T[K % D]);
         // (the scheduler must not move later fetches or terms across)
         if constexpr (K < 7) __builtin_amdgcn_sched_barrier(0);
-        hop_terms<K + 1, D, SP, LK, NR, DAG, UNI>(a, rid, i, c, T, acc, before_last);
+        hop_terms<K + 1, D, SP, LK, NR, DAG>(a, src, rid, i, c, T, acc, before_last);
     }
+}
+
+// acc = the hopping term at output site i for the NR RHS of a lane, D terms in
+// flight.  The result is opaque: the terms must not be moved into the branch
+// of the stores, past the scheduling barriers.
+template <int D, int SP, int LK, int NR, bool DAG, class SRC, typename real, class F>
+__device__ __forceinline__ void hop_ahead(const DslashArgs &a, const SRC &src, const int rid[NR], int i,
+                                          const int c[4], real acc[NR][24], F &&before_last)
+{
+    TermRaw<SRC, LK, NR> T[D];
+    fetch_first<0, D, LK, NR>(a, src, rid, i, c, T);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+#pragma unroll
+        for (int k = 0; k < 24; k++) acc[r][k] = 0;
+    hop_terms<0, D, SP, LK, NR, DAG>(a, src, rid, i, c, T, acc, before_last);
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+#pragma unroll
+        for (int k = 0; k < 24; k++) asm volatile("" : "+v"(acc[r][k]));
 }
 
 // Terms in flight (of depths 1 to 4; times in us, depth 0 the compiler's own
@@ -607,27 +638,12 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
         if constexpr (UNI) rid[r] = __builtin_amdgcn_readfirstlane(rid[r]);
     }
 
-    constexpr int D = terms_ahead<SP, NR>();
     int c[4];
     site_coords(a.g, i, a.P, c);
-    TermRaw<SP, LK, NR> T[D];
-    fetch_first<0, D, SP, LK, NR, UNI>(a, rid, i, c, T);
-    __builtin_amdgcn_sched_barrier(0);
-    real acc[NR][24];
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-#pragma unroll
-        for (int k = 0; k < 24; k++) acc[r][k] = 0;
-    real x[24], rr[24];
-    hop_terms<0, D, SP, LK, NR, DAG, UNI>(a, rid, i, c, T, acc, [&] {
+    real acc[NR][24], x[24], rr[24];
+    hop_ahead<terms_ahead<SP, NR>(), SP, LK, NR, DAG>(a, PackedSrc<SP, UNI>{}, rid, i, c, acc, [&] {
         if constexpr (NR == 1) epi_load<SP, EPI>(a, i, rid[0], x, rr);
     });
-    // (opaque: the terms must not be moved into the branch of the stores, past
-    // the barriers above)
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-#pragma unroll
-        for (int k = 0; k < 24; k++) asm volatile("" : "+v"(acc[r][k]));
     if constexpr (NR == 1)
         epi_finish<SP, RL, EPI>(a, i, live && rv[0], rid[0], acc[0], x, rr);
     else

@@ -18,33 +18,31 @@ namespace wd {
 // only their alignment is taken for granted.
 typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
 
-// Neighbour source: the canonical complex128 field, 24 consecutive doubles a
-// site.  full: lex order of the whole lattice (site 2 * cb + the low bit of
-// x), else the cb order of one parity.
-template <int SP>
-struct CanonNb {
-    const double *base;
-    bool full;
-    int xbit;  // low bit of the output site's x
+// Source of the terms' spinors: the canonical complex128 field, 24 consecutive
+// doubles a site.  full: lex order of the whole lattice (site 2 * cb + the low
+// bit of x), else the cb order of one parity.  A neighbour is encoded to the
+// storage format as it is used.
+struct CanonRaw { dbl2u_t w[12]; };
 
-    template <int MU>
-    __device__ __forceinline__ void load(int j, double v[24]) const
+template <int SP, int NR>
+struct CanonNb {
+    const CanonRaw (&s)[NR];
+
+    template <typename real>
+    __device__ __forceinline__ void values(int r, real v[24]) const
     {
-        const long long site = full ? 2LL * j + (MU == 0 ? xbit ^ 1 : xbit) : (long long)j;
-        const dbl2u_t *p = reinterpret_cast<const dbl2u_t *>(base + site * 24);
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            const dbl2u_t w = p[k];
-            v[2 * k] = w.x;
-            v[2 * k + 1] = w.y;
+            v[2 * k] = (real)s[r].w[k].x;
+            v[2 * k + 1] = (real)s[r].w[k].y;
         }
     }
     template <int MU, int DIR>
-    __device__ __forceinline__ float half(const DslashArgs &, int, int, int j, _Float16 v[24]) const
+    __device__ __forceinline__ float half(const DslashArgs &, int, int r, int, _Float16 v[24]) const
     {
         double d[24];
         uint32_t w[12];
-        load<MU>(j, d);
+        values(r, d);
         const float m = SpinorIO<SP_F16>::encode(d, w);
 #pragma unroll
         for (int k = 0; k < 12; k++) {
@@ -54,22 +52,22 @@ struct CanonNb {
         return m;
     }
     template <int MU, int DIR>
-    __device__ __forceinline__ float h2(const DslashArgs &, int, int, int j, h2_t v[12]) const
+    __device__ __forceinline__ float h2(const DslashArgs &, int, int r, int, h2_t v[12]) const
     {
         double d[24];
         uint32_t w[12];
-        load<MU>(j, d);
+        values(r, d);
         const float m = SpinorIO<SP_F16>::encode(d, w);
 #pragma unroll
         for (int k = 0; k < 12; k++) v[k] = __builtin_bit_cast(h2_t, w[k]);
         return m;
     }
     template <int MU, int DIR>
-    __device__ __forceinline__ float i16(const DslashArgs &, int, int, int j, int v[24]) const
+    __device__ __forceinline__ float i16(const DslashArgs &, int, int r, int, int v[24]) const
     {
         double d[24];
         uint32_t w[12];
-        load<MU>(j, d);
+        values(r, d);
         const float m = SpinorIO<SP_I16>::encode(d, w);
 #pragma unroll
         for (int k = 0; k < 12; k++) {
@@ -79,13 +77,28 @@ struct CanonNb {
         return SpinorIO<SP_I16>::step(m);
     }
     template <int MU, int DIR, int SP_, typename real>
-    __device__ __forceinline__ real gen(const DslashArgs &, int, int, int j, real v[24]) const
+    __device__ __forceinline__ real gen(const DslashArgs &, int, int r, int, real v[24]) const
     {
-        double d[24];
-        load<MU>(j, d);
-#pragma unroll
-        for (int k = 0; k < 24; k++) v[k] = (real)d[k];
+        values(r, v);
         return (real)1;
+    }
+};
+
+template <int SP>
+struct CanonSrc {
+    const double *base;
+    bool full;
+    int xbit;  // low bit of the output site's x
+
+    typedef CanonRaw Raw;
+    template <int NR> using Nb = CanonNb<SP, NR>;
+    template <int MU>
+    __device__ __forceinline__ void fetch(const DslashArgs &, int, int j, Raw &R) const
+    {
+        const long long site = full ? 2LL * j + (MU == 0 ? xbit ^ 1 : xbit) : (long long)j;
+        const dbl2u_t *p = reinterpret_cast<const dbl2u_t *>(base + site * 24);
+#pragma unroll
+        for (int k = 0; k < 12; k++) R.w[k] = p[k];
     }
 };
 
@@ -115,12 +128,13 @@ __device__ __forceinline__ void stored_values(const real v[24], double d[24])
 // small lattices spread over more CUs, and at 24^3 x 24 and above 64 threads
 // are still 2-5 % faster than 128.  CIN: neighbours (and the xpay operand)
 // from the canonical field, else from the structure of arrays; the host's
-// rule is op_reads_canonical.  A call is bound by its launches up to about
-// 12^3 x 24 and by the links' bytes above.  Against pack, sweep and unpack
-// with uploads of ids and coefficients: FP64 D_eo on 4^4 36.8 -> 10.2 us a
-// call, FP16 on 10 x 14 x 6 x 22 44.7 -> 10.3 us, Mhat^dag Mhat on 16^3 x 32
-// 119 -> 70 us, FP64 18-real D_oe^dag on 32^3 x 64 572 -> 414 us (1.6 GB,
-// 3.9 TB/s).
+// rule is op_reads_canonical.  Two terms are in flight from the canonical
+// field (48 registers each for the spinor).  A call is bound by its launches
+// up to about 12^3 x 24 and by the links' bytes above.  Against pack, sweep and
+// unpack with uploads of ids and coefficients, then with terms fetched ahead:
+// FP64 D_eo on 4^4 36.8 -> 10.2 -> 10 us a call, Mhat^dag Mhat on 16^3 x 32 119
+// -> 66 -> 64, FP64 18-real D_oe^dag on 32^3 x 64 572 -> 412 -> 374 (1.6 GB, 4.3
+// TB/s).
 template <int SP, int LK, bool DAG, bool CIN>
 __global__ void __launch_bounds__(256) dslash_op_kernel(OpArgs o)
 {
@@ -128,8 +142,9 @@ __global__ void __launch_bounds__(256) dslash_op_kernel(OpArgs o)
     const int L = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int tile = o.np == 2 ? L >> 1 : L;
     const int P = o.np == 2 ? L & 1 : o.P0;
-    const int i = tile * (int)blockDim.x + (int)threadIdx.x;
-    if (i >= o.g.Vh) return;
+    const int i0 = tile * (int)blockDim.x + (int)threadIdx.x;
+    const bool live = i0 < o.g.Vh;
+    const int i = live ? i0 : o.g.Vh - 1;  // (lanes past the end compute the last site and store nothing)
     const long long rid = blockIdx.y;
     DslashArgs a;
     a.g = o.g;
@@ -138,26 +153,17 @@ __global__ void __launch_bounds__(256) dslash_op_kernel(OpArgs o)
     a.in_rs = 0;
     int c[4];
     site_coords(o.g, i, P, c);
+    const long long site = o.full ? 2LL * i + (c[0] & 1) : (long long)i;
     const int one[1] = {0};
     real acc[1][24];
-#pragma unroll
-    for (int k = 0; k < 24; k++) acc[0][k] = 0;
     if constexpr (CIN) {
         a.in = nullptr;
-        const CanonNb<SP> nb{reinterpret_cast<const double *>(o.in) + rid * o.in_rs, o.full != 0, c[0] & 1};
-        hop_dir<0, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<1, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<2, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<3, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
+        const CanonSrc<SP> src{reinterpret_cast<const double *>(o.in) + rid * o.in_rs, o.full != 0, c[0] & 1};
+        hop_ahead<2, SP, LK, 1, DAG>(a, src, one, i, c, acc, [] {});
     } else {
         a.in = o.in + rid * o.in_rs + (1 - P) * o.in_ss;
-        const GlobalNb<true> nb;
-        hop_dir<0, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<1, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<2, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
-        hop_dir<3, SP, LK, 1, DAG>(a, nb, i, c, one, acc);
+        hop_ahead<terms_ahead<SP, 1>(), SP, LK, 1, DAG>(a, PackedSrc<SP, true>{}, one, i, c, acc, [] {});
     }
-    const long long site = o.full ? 2LL * i + (c[0] & 1) : (long long)i;
     if constexpr (SP == SP_F64) {
         if (o.xpay) {
             double xv[24];
@@ -177,6 +183,7 @@ __global__ void __launch_bounds__(256) dslash_op_kernel(OpArgs o)
             for (int k = 0; k < 24; k++) acc[0][k] = fmaT(o.coef, acc[0][k], xv[k]);
         }
     }
+    if (!live) return;
     if (o.outcanon) {
         double d[24];
         stored_values<SP>(acc[0], d);

@@ -63,9 +63,8 @@ extern "C" wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, 
     if (!std::isfinite(kappa)) return set_error(WD_ERR_ARG, "kappa not finite");
     char *base = (char *)scratch_ptr(c->device);
     if (!base) return set_error(WD_ERR_STATE, "no device scratch on device %d (context not from wd_create?)", c->device);
-    // wd_mdagm's packed FP64 operand A and temporaries T, B: the full
-    // operator uses both parity subfields of each (6 subfields), the
-    // even-odd one subfield of A and B and both of T (4)
+    // temporaries T and B of wd_mdagm, and the limit that callers know: 6
+    // subfields for the full operator, 4 for the even-odd one
     const long long sub = ((long long)spinor_site_bytes(SP_F64) * c->g.cs + 255) / 256 * 256;
     const size_t need = kHeadBytes + (size_t)((eo ? 4 : 6) * sub);
     if (need > kScratchBytes)
@@ -80,14 +79,13 @@ extern "C" wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, 
     f.cs = c->g.cs;
     f.ss = sub;
     f.rs = 2 * sub;
-    Field A = f, T = f, B = f;
-    A.base = base + kHeadBytes;
-    T.base = A.base + (eo ? 1 : 2) * sub;
+    Field T = f, B = f;
+    T.base = base + kHeadBytes;
     B.base = T.base + 2 * sub;
     // no per-launch timing events here (event creation allocates)
     const bool timing = c->timing;
     c->timing = false;
-    const wd_status st = mdagm_apply(c, out, in, kappa, eo, A, T, B);
+    const wd_status st = mdagm_apply(c, out, in, kappa, eo, T, B);
     c->timing = timing;
     return st;
 }

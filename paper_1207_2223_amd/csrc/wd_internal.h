@@ -372,13 +372,11 @@ double sweep_bytes(const wd_ctx *c, const Sweep &sw);
 // One operator sweep of nrhs right-hand sides (g and links are filled in), and
 // whether a call on this lattice reads canonical input in its first sweep.
 wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs);
-bool op_reads_canonical(const wd_ctx *c, int sp, int lk, int np, const void *in, const void *out, size_t in_bytes,
+bool op_reads_canonical(const wd_ctx *c, int sp, int np, const void *in, const void *out, size_t in_bytes,
                         size_t out_bytes);
 // M^dag M or Mhat^dag Mhat of a canonical FP64 field through FP64 buffers of
-// one (eo) or two subfields: A (the packed operand, unless the lattice is read
-// canonically), T and B.
-wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &A, const Field &T,
-                      const Field &B);
+// one (eo) or two subfields, T and B.
+wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &T, const Field &B);
 // The allocation-free entry points' device scratch array (noalloc.hip): its
 // address on `device` is looked up once, with that device current (called by
 // wd_create), and kept per device.
