@@ -764,6 +764,26 @@ wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, in
     return op_sweep(c, d, SP_F64, c->lk64, 1, 1);
 }
 
+wd_status mhat_dag_apply(wd_ctx *c, double *out, const double *in, double *T, double kappa, int nrhs)
+{
+    OpArgs s1;  // T = D_oe^dag in
+    s1.P0 = 1;
+    s1.incanon = s1.outcanon = 1;
+    s1.in = (const char *)in;
+    s1.out = (char *)T;
+    s1.in_rs = s1.out_rs = c->Vh * 24;
+    WD_TRY(op_sweep(c, s1, SP_F64, c->lk64, 1, nrhs));
+    OpArgs s2 = s1;  // out = in - k^2 D_eo^dag T
+    s2.P0 = 0;
+    s2.in = (const char *)T;
+    s2.out = (char *)out;
+    s2.xpay = s2.xcanon = 1;
+    s2.coef = -kappa * kappa;
+    s2.x = (const char *)in;
+    s2.x_rs = c->Vh * 24;
+    return op_sweep(c, s2, SP_F64, c->lk64, 1, nrhs);
+}
+
 }  // namespace wd
 }  // extern "C++"
 

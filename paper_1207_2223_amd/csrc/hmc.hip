@@ -436,18 +436,6 @@ __global__ void __launch_bounds__(1024) k_sum(const double *partial, int n, doub
     if (threadIdx.x == 0) out[0] = sh[0];
 }
 
-// even-odd split/merge of canonical spinors: full[lex] <-> parity fields [cb]
-__global__ void __launch_bounds__(kB) k_merge(const double *e, const double *o, double *full, Geom g)
-{
-    const int x = blockIdx.x * kB + threadIdx.x;
-    if (x >= 2 * g.Vh) return;
-    int c[4];
-    coords_lex(g, x, c);
-    const int P = (c[0] + c[1] + c[2] + c[3]) & 1;
-    const double *src = (P ? o : e) + (size_t)(x >> 1) * 24;
-    for (int k = 0; k < 24; k++) full[(size_t)x * 24 + k] = src[k];
-}
-
 }  // namespace
 
 }  // namespace wd
@@ -532,31 +520,6 @@ wd_status plaquette_host(wd_ctx *c, HmcWs &w, const double *U, double *plaq)
     return WD_OK;
 }
 
-// out (even parity, canonical) = Mhat^dag in  (FP64 stencil sweeps)
-wd_status mhat_dag(wd_ctx *c, const double *in_e, double *out_e, double kappa)
-{
-    Field A, T, B;
-    WD_TRY(alloc_field(c, "hmc_fa", SP_F64, 1, 1, &A));
-    WD_TRY(alloc_field(c, "hmc_ft", SP_F64, 1, 1, &T));
-    WD_TRY(alloc_field(c, "hmc_fb", SP_F64, 1, 1, &B));
-    double cf = -kappa * kappa;
-    double *dcf;
-    WD_TRY(upload_doubles(c, "hmc_coef", &cf, 1, &dcf));
-    int zero = 0;
-    int *act;
-    WD_TRY(upload_ints(c, "hmc_act", &zero, 1, &act));
-    HIPCHK(pack_spinor(in_e, A, 1, 0, c->g, c->stream));
-    Sweep sw;
-    sw.sp = SP_F64; sw.lk = c->lk64; sw.active = act; sw.nact = 1; sw.coef = dcf;
-    sw.dag = 1;
-    sw.P = 1; sw.epi = EPI_PLAIN; sw.in = A; sw.out = T;
-    WD_TRY(run_sweep(c, sw, nullptr));
-    sw.P = 0; sw.epi = EPI_XPAY; sw.in = T; sw.x = A; sw.out = B;
-    WD_TRY(run_sweep(c, sw, nullptr));
-    HIPCHK(unpack_spinor(B, out_e, 1, 0, c->g, c->stream));
-    return WD_OK;
-}
-
 // one parity block of H (or H^dag) on canonical parity fields, FP64
 wd_status hop_block(wd_ctx *c, const double *in, double *out, int out_par, int dag)
 {
@@ -577,18 +540,16 @@ wd_status md_force(wd_ctx *c, HmcWs &w, double beta, double kappa, const wd_solv
     if (s != WD_OK) return s;
     // Y_e = Mhat X_e = X_e - k^2 D_eo D_oe X_e ;  X_o = D_oe X_e ;  Y_o = (H^dag)_oe Y_e
     WD_TRY(hop_block(c, w.Xe, w.Xo, 1, 0));
-    WD_TRY(hop_block(c, w.Xo, w.tmp, 0, 0));
-    {
-        const double k2 = kappa * kappa;
-        // Ye = Xe - k2 tmp : reuse k_p_step (P -= eps F) on copies
-        HIPCHK(hipMemcpyAsync(w.Ye, w.Xe, w.ns * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-        hipLaunchKernelGGL(k_p_step, dim3(nblk((long long)w.ns)), dim3(kB), 0, c->stream, w.Ye, w.tmp,
-                           (long long)w.ns, k2);
-        HIPCHK(hipGetLastError());
-    }
+    OpArgs o;
+    o.incanon = o.xpay = o.xcanon = o.outcanon = 1;
+    o.in = (const char *)w.Xo;
+    o.coef = -kappa * kappa;
+    o.x = (const char *)w.Xe;
+    o.out = (char *)w.Ye;
+    WD_TRY(op_sweep(c, o, SP_F64, c->lk64, 0, 1));
     WD_TRY(hop_block(c, w.Ye, w.Yo, 1, 1));
-    hipLaunchKernelGGL(k_merge, dim3(nblk(2 * c->Vh)), dim3(kB), 0, c->stream, w.Xe, w.Xo, w.Xf, c->g);
-    hipLaunchKernelGGL(k_merge, dim3(nblk(2 * c->Vh)), dim3(kB), 0, c->stream, w.Ye, w.Yo, w.Yf, c->g);
+    HIPCHK(merge_parities(w.Xe, w.Xo, 1.0, w.Xf, 1, c->g, c->stream));
+    HIPCHK(merge_parities(w.Ye, w.Yo, 1.0, w.Yf, 1, c->g, c->stream));
     hipLaunchKernelGGL(k_fermion_force, dim3(nblk(nl)), dim3(kB), 0, c->stream, w.U, w.Xf, w.Yf, w.F, c->g,
                        -2.0 * kappa * kappa);
     HIPCHK(hipGetLastError());
@@ -692,7 +653,7 @@ wd_status hmc_trajectory(wd_ctx *c, double *U, const wd_hmc_params *h, wd_hmc_re
     HIPCHK(hipMemcpyAsync(w.U, U, w.nl * sizeof(double), hipMemcpyDeviceToDevice, s));
     WD_TRY(reload_links(c, w.U));
     WD_TRY(wd_hmc_draw(c, w.P, w.chi, h->seed, h->traj));
-    WD_TRY(mhat_dag(c, w.chi, w.phi, kappa));
+    WD_TRY(mhat_dag_apply(c, w.phi, w.chi, w.tmp, kappa, 1));
 
     double kin0, plaq0, chi2;
     WD_TRY(dot_host(c, w, w.P, w.P, (long long)w.nl, &kin0));  // sum |P_ij|^2 = tr P^2

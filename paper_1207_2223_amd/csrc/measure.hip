@@ -41,47 +41,11 @@ __global__ void __launch_bounds__(kB) k_fill(double *a, double v, long long n)
     if (i < n) a[i] = v;
 }
 
-// y = a x + y
-__global__ void __launch_bounds__(kB) k_axpy(double *y, const double *x, double a, long long n)
-{
-    const long long i = (long long)blockIdx.x * kB + threadIdx.x;
-    if (i < n) y[i] = fmaT(a, x[i], y[i]);
-}
-
-__global__ void __launch_bounds__(kB) k_scale(double *y, double a, long long n)
-{
-    const long long i = (long long)blockIdx.x * kB + threadIdx.x;
-    if (i < n) y[i] *= a;
-}
-
-// column j of a [12][sites][4][3] parity field gets +1 at (site, spin-colour j)
+// column j of a [12][sites][4][3] field gets +1 at (site, spin-colour j)
 __global__ void k_add_point(double *b, int site, long long col_doubles)
 {
     const int j = threadIdx.x;
     if (j < 12) b[(size_t)j * col_doubles + (size_t)site * 24 + 2 * j] += 1.0;
-}
-
-// one column [sites][4][3] gets +1 at (site, spin-colour j)
-__global__ void k_add_one(double *b, int site, int j)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) b[(size_t)site * 24 + 2 * j] += 1.0;
-}
-
-// full[lex] <- e[cb] or o[cb] by the parity of lex (canonical layouts)
-__global__ void __launch_bounds__(kB) k_merge(const double *e, const double *o, double *full, Geom g)
-{
-    const int x = blockIdx.x * kB + threadIdx.x;
-    if (x >= 2 * g.Vh) return;
-    int r = x;
-    const int c0 = r % g.L[0];
-    r /= g.L[0];
-    const int c1 = r % g.L[1];
-    r /= g.L[1];
-    const int c2 = r % g.L[2];
-    const int c3 = r / g.L[2];
-    const double *src = (((c0 + c1 + c2 + c3) & 1) ? o : e) + (size_t)(x >> 1) * 24;
-#pragma unroll
-    for (int k = 0; k < 24; k++) full[(size_t)x * 24 + k] = src[k];
 }
 
 // Fixed-order block sum of kB values (tree over shared memory).
@@ -258,7 +222,7 @@ extern "C" wd_status wd_point_propagator(wd_ctx *c, double *psi, const int32_t s
     if (!p.eo) return set_error(WD_ERR_ARG, "the propagator uses the even-odd solve (eo = 1)");
     WD_HIP(hipSetDevice(c->device));
     const hipStream_t s = c->stream;
-    const long long Vh = c->Vh, V = 2 * Vh, col = Vh * 24;  // doubles per parity column
+    const long long col = c->Vh * 24;  // doubles per parity column
     const int x0 = src[0] + c->dims[0] * (src[1] + c->dims[1] * (src[2] + c->dims[2] * src[3]));
     const int par = (src[0] + src[1] + src[2] + src[3]) & 1, cb0 = x0 >> 1;
     void *vp;
@@ -266,44 +230,41 @@ extern "C" wd_status wd_point_propagator(wd_ctx *c, double *psi, const int32_t s
     double *A = (double *)vp;  // bhat, then the even solution
     WD_TRY(ws_get(c, "ms_b", sizeof(double) * 12 * col, &vp));
     double *B = (double *)vp;  // Mhat^dag bhat
-    WD_TRY(ws_get(c, "ms_t", sizeof(double) * 3 * col, &vp));
-    double *T1 = (double *)vp, *T2 = T1 + col, *PO = T2 + col;
-
+    // (the twelve columns of a step in one launch; psi, written last, holds
+    // intermediate parity columns)
     // bhat_j = b_e + k D_eo b_o
     hipLaunchKernelGGL(k_fill, dim3(nblk(12 * col)), dim3(kB), 0, s, A, 0.0, 12 * col);
-    HIPCHK(hipGetLastError());
     if (par == 0) {
         hipLaunchKernelGGL(k_add_point, dim3(1), dim3(64), 0, s, A, cb0, col);
     } else {
-        for (int j = 0; j < 12; j++) {
-            hipLaunchKernelGGL(k_fill, dim3(nblk(col)), dim3(kB), 0, s, PO, 0.0, col);
-            hipLaunchKernelGGL(k_add_one, dim3(1), dim3(64), 0, s, PO, cb0, j);
-            WD_TRY(wd_dslash(c, A + (size_t)j * col, PO, WD_EVEN, 0, WD_F64));
-            hipLaunchKernelGGL(k_scale, dim3(nblk(col)), dim3(kB), 0, s, A + (size_t)j * col, kappa, col);
-        }
+        hipLaunchKernelGGL(k_fill, dim3(nblk(12 * col)), dim3(kB), 0, s, psi, 0.0, 12 * col);
+        hipLaunchKernelGGL(k_add_point, dim3(1), dim3(64), 0, s, psi, cb0, col);
+        OpArgs o;
+        o.incanon = o.xpay = o.xcanon = o.outcanon = 1;
+        o.in = (const char *)psi;
+        o.coef = kappa;
+        o.x = (const char *)A;
+        o.out = (char *)A;
+        o.in_rs = o.x_rs = o.out_rs = col;
+        WD_TRY(op_sweep(c, o, SP_F64, c->lk64, 0, 12));
     }
     HIPCHK(hipGetLastError());
-    // B_j = Mhat^dag bhat_j = bhat_j - k^2 D_oe^dag D_eo^dag bhat_j
-    for (int j = 0; j < 12; j++) {
-        double *a = A + (size_t)j * col, *b = B + (size_t)j * col;
-        WD_TRY(wd_dslash(c, T1, a, WD_ODD, 1, WD_F64));
-        WD_TRY(wd_dslash(c, T2, T1, WD_EVEN, 1, WD_F64));
-        HIPCHK(hipMemcpyAsync(b, a, sizeof(double) * col, hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_axpy, dim3(nblk(col)), dim3(kB), 0, s, b, T2, -kappa * kappa, col);
-    }
-    HIPCHK(hipGetLastError());
+    // B_j = Mhat^dag bhat_j
+    WD_TRY(mhat_dag_apply(c, B, A, psi, kappa, 12));
     // psi_e: the batched solve of all 12 columns
     std::vector<double> kap(12, kappa);
     const wd_status sst = wd_cg_solve(c, A, B, 12, kap.data(), &p, st);
     if (sst != WD_OK && sst != WD_ERR_NOCONV && sst != WD_ERR_NAN) return sst;
     // psi_o = b_o + k D_oe psi_e, merged with psi_e into the full columns
-    for (int j = 0; j < 12; j++) {
-        const double *e = A + (size_t)j * col;
-        WD_TRY(wd_dslash(c, T1, e, WD_ODD, 0, WD_F64));
-        hipLaunchKernelGGL(k_scale, dim3(nblk(col)), dim3(kB), 0, s, T1, kappa, col);
-        if (par == 1) hipLaunchKernelGGL(k_add_one, dim3(1), dim3(64), 0, s, T1, cb0, j);
-        hipLaunchKernelGGL(k_merge, dim3(nblk(V)), dim3(kB), 0, s, e, T1, psi + (size_t)j * V * 24, c->g);
-    }
+    OpArgs o;
+    o.P0 = 1;
+    o.incanon = o.outcanon = 1;
+    o.in = (const char *)A;
+    o.out = (char *)B;
+    o.in_rs = o.out_rs = col;
+    WD_TRY(op_sweep(c, o, SP_F64, c->lk64, 0, 12));
+    HIPCHK(merge_parities(A, B, kappa, psi, 12, c->g, s));
+    if (par == 1) hipLaunchKernelGGL(k_add_point, dim3(1), dim3(64), 0, s, psi, x0, 2 * col);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s));
     if (sst != WD_OK) set_error(sst, "%s", sst == WD_ERR_NAN ? "non-finite residual" : "not converged");

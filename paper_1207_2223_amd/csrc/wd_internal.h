@@ -377,6 +377,12 @@ bool op_reads_canonical(const wd_ctx *c, int sp, int np, const void *in, const v
 // M^dag M or Mhat^dag Mhat of a canonical FP64 field through FP64 buffers of
 // one (eo) or two subfields, T and B.
 wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &T, const Field &B);
+// out = Mhat^dag in for nrhs canonical FP64 even-parity columns; T: scratch
+// columns of the same size.
+wd_status mhat_dag_apply(wd_ctx *c, double *out, const double *in, double *T, double kappa, int nrhs);
+// full-lattice columns from parity columns, the odd ones times so (pack.hip)
+hipError_t merge_parities(const double *e, const double *o, double so, double *full, int ncol, const Geom &g,
+                          hipStream_t s);
 // The allocation-free entry points' device scratch array (noalloc.hip): its
 // address on `device` is looked up once, with that device current (called by
 // wd_create), and kept per device.

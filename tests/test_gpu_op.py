@@ -84,3 +84,29 @@ def test_normal_operator_in_place_and_from_an_unaligned_field(wd, oracle, recon,
         wd._check(wd.lib().wd_mdagm(lat.ctx, ctypes.c_void_p(odd.data_ptr() + 8), ctypes.c_void_p(buf.data_ptr() + 8), 0.14, eo))
         assert np.array_equal(host(odd[1:]), torch.view_as_real(out).reshape(-1).cpu().numpy())
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 6, 4, 10), (4, 4, 4, 4)])
+@pytest.mark.parametrize("src", [(0, 2, 1, 3), (1, 2, 1, 3)])
+def test_propagator_columns_solve_the_full_operator(dims, src):
+    """M psi_j = point_j for the twelve columns put together from their parity
+    halves, both source parities, a site count that leaves the last work-group
+    of the merge part empty.  |1 - Mhat| <= (8 kappa)^2 = 0.77, so the solve's
+    1e-12 is a residual below 1.5e-11 here."""
+    import torch
+    from paper_1207_2223_amd import wd
+    V, kappa = li.volume(dims), 0.11
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.5, seed=71)), recon=18)
+    psi = torch.empty((12, V, 4, 3), dtype=torch.complex128, device="cuda")
+    st, _ = lat.point_propagator(psi, src, kappa, wd.solver_params(prec=wd.WD_F64, tol=1e-12))
+    assert st == wd.WD_OK
+    x0 = src[0] + dims[0] * (src[1] + dims[1] * (src[2] + dims[2] * src[3]))
+    hop = torch.empty_like(psi[0])
+    for j in range(12):
+        lat.dslash(hop, psi[j], 0, 0, 0)
+        r = psi[j] - kappa * hop
+        r.view(V, 12)[x0, j] -= 1.0
+        note(f"propagator {dims} {src} column {j}")
+        assert float(torch.linalg.vector_norm(r)) <= 1e-10
+    lat.close()
