@@ -32,105 +32,54 @@
 
 namespace wd {
 
-// Neighbour spinor in compute precision.  For FP16 the per-site norm is
-// returned separately (scale) so that it can be applied after projection.
-template <int SP, typename real>
-__device__ __forceinline__ real load_nb(const char *f, int cs, int j, real v[24])
-{
-    if constexpr (SP == SP_F16) {
-        const half8_t *p = reinterpret_cast<const half8_t *>(f);
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            half8_t w = p[(size_t)k * cs + j];
-#pragma unroll
-            for (int q = 0; q < 8; q++) v[8 * k + q] = (real)(float)w[q];
-        }
-        return (real)reinterpret_cast<const float *>(f + (size_t)48 * cs)[j];
-    } else if constexpr (SP == SP_I16) {
-        const short8_t *p = reinterpret_cast<const short8_t *>(f);
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            short8_t w = p[(size_t)k * cs + j];
-#pragma unroll
-            for (int q = 0; q < 8; q++) v[8 * k + q] = (real)(float)w[q];
-        }
-        return (real)SpinorIO<SP_I16>::step(reinterpret_cast<const float *>(f + (size_t)48 * cs)[j]);
-    } else {
-        SpinorIO<SP>::load(f, cs, j, v);
-        return (real)1;
-    }
-}
-
-// FP16 neighbour spinor as stored (24 halves), and its per-site norm; UNI:
-// the field base is the same in every lane.
-template <bool UNI>
+// FP16 neighbour spinor as stored (24 halves), and its per-site norm; the
+// field base is the same in every lane.
 __device__ __forceinline__ float load_nb_half(const char *f, int cs, int j, _Float16 v[24])
 {
-    const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
+    const uint32_t off = pin_v((uint32_t)j * 16u);
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-        const half8_t w = ld_off<half8_t, UNI>(f + (size_t)k * cs * 16, off);
+        const half8_t w = ld_off<half8_t, true>(f + (size_t)k * cs * 16, off);
 #pragma unroll
         for (int q = 0; q < 8; q++) v[8 * k + q] = w[q];
     }
-    return ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u);
-}
-
-// int16 neighbour spinor as stored (widened to int), and its quantisation
-// step (norm / 32767).
-template <bool UNI>
-__device__ __forceinline__ float load_nb_i16(const char *f, int cs, int j, int v[24])
-{
-    const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
-#pragma unroll
-    for (int k = 0; k < 3; k++) {
-        const short8_t w = ld_off<short8_t, UNI>(f + (size_t)k * cs * 16, off);
-#pragma unroll
-        for (int q = 0; q < 8; q++) v[8 * k + q] = w[q];
-    }
-    return SpinorIO<SP_I16>::step(ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u));
+    return ld_off<float, true>(f + (size_t)48 * cs, pin_v((uint32_t)j * 4u));
 }
 
 // FP16 neighbour spinor as 12 (re, im) half2 pairs, and its per-site norm.
-template <bool UNI>
 __device__ __forceinline__ float load_nb_h2(const char *f, int cs, int j, h2_t v[12])
 {
-    const uint32_t off = UNI ? pin_v((uint32_t)j * 16u) : (uint32_t)j * 16u;
+    const uint32_t off = pin_v((uint32_t)j * 16u);
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-        const half8_t w = ld_off<half8_t, UNI>(f + (size_t)k * cs * 16, off);
+        const half8_t w = ld_off<half8_t, true>(f + (size_t)k * cs * 16, off);
 #pragma unroll
         for (int q = 0; q < 4; q++) v[4 * k + q] = h2_t{w[2 * q], w[2 * q + 1]};
     }
-    return ld_off<float, UNI>(f + (size_t)48 * cs, UNI ? pin_v((uint32_t)j * 4u) : (uint32_t)j * 4u);
+    return ld_off<float, true>(f + (size_t)48 * cs, pin_v((uint32_t)j * 4u));
 }
 
 // Where a sweep reads the neighbour spinors.  GlobalNb: from the input field
-// in global memory, for every direction (UNI: the field base is the same in
-// every lane).  Each load returns the values as stored and the per-site scale
+// in global memory, for every direction (its base is the same in every lane).
+// Each load returns the values as stored and the per-site scale
 // of the format (1 without a norm); rid is the RHS id, r its index in the
 // lane's group, j the neighbour's checkerboard index.
-template <bool UNI>
 struct GlobalNb {
     template <int MU, int DIR>
     __device__ __forceinline__ float half(const DslashArgs &a, int rid, int, int j, _Float16 v[24]) const
     {
-        return load_nb_half<UNI>(a.in + rid * a.in_rs, a.g.cs, j, v);
+        return load_nb_half(a.in + rid * a.in_rs, a.g.cs, j, v);
     }
     template <int MU, int DIR>
     __device__ __forceinline__ float h2(const DslashArgs &a, int rid, int, int j, h2_t v[12]) const
     {
-        return load_nb_h2<UNI>(a.in + rid * a.in_rs, a.g.cs, j, v);
-    }
-    template <int MU, int DIR>
-    __device__ __forceinline__ float i16(const DslashArgs &a, int rid, int, int j, int v[24]) const
-    {
-        return load_nb_i16<UNI>(a.in + rid * a.in_rs, a.g.cs, j, v);
+        return load_nb_h2(a.in + rid * a.in_rs, a.g.cs, j, v);
     }
     template <int MU, int DIR, int SP, typename real>
     __device__ __forceinline__ real gen(const DslashArgs &a, int rid, int, int j, real v[24]) const
     {
-        return load_nb<SP>(a.in + rid * a.in_rs, a.g.cs, j, v);
+        SpinorIO<SP>::load(a.in + rid * a.in_rs, a.g.cs, j, v);
+        return (real)1;
     }
 };
 
@@ -160,7 +109,7 @@ struct LdsNb {
     __device__ __forceinline__ float half(const DslashArgs &a, int rid, int r, int j, _Float16 v[24]) const
     {
         if constexpr (MU == 2) {
-            return GlobalNb<true>{}.template half<MU, DIR>(a, rid, r, j, v);
+            return GlobalNb{}.template half<MU, DIR>(a, rid, r, j, v);
         } else {
             int jl;
             const lds_char *p = at<MU, DIR>(r, j, &jl);
@@ -177,7 +126,7 @@ struct LdsNb {
     __device__ __forceinline__ float h2(const DslashArgs &a, int rid, int r, int j, h2_t v[12]) const
     {
         if constexpr (MU == 2) {
-            return GlobalNb<true>{}.template h2<MU, DIR>(a, rid, r, j, v);
+            return GlobalNb{}.template h2<MU, DIR>(a, rid, r, j, v);
         } else {
             int jl;
             const lds_char *p = at<MU, DIR>(r, j, &jl);
@@ -190,16 +139,11 @@ struct LdsNb {
             return *(const __attribute__((address_space(3))) float *)(p + 48 * S + jl * 4);
         }
     }
-    template <int MU, int DIR>
-    __device__ __forceinline__ float i16(const DslashArgs &a, int rid, int r, int j, int v[24]) const
-    {
-        return GlobalNb<true>{}.template i16<MU, DIR>(a, rid, r, j, v);  // (no LDS variant for int16)
-    }
     template <int MU, int DIR, int SP_, typename real>
     __device__ __forceinline__ real gen(const DslashArgs &a, int rid, int r, int j, real v[24]) const
     {
         if constexpr (MU == 2 || SP_ != SP_F32) {
-            return GlobalNb<true>{}.template gen<MU, DIR, SP_>(a, rid, r, j, v);
+            return GlobalNb{}.template gen<MU, DIR, SP_>(a, rid, r, j, v);
         } else {
             int jl;
             const lds_char *p = at<MU, DIR>(r, j, &jl);
@@ -883,7 +827,7 @@ struct TwNb {
                 for (int e = 0; e < 8; e++) v[8 * k + e] = C.ch[r][k][e];
             return C.nrm[r];
         } else {
-            return GlobalNb<true>{}.template half<MU, DIR>(a, rid, r, j, v);
+            return GlobalNb{}.template half<MU, DIR>(a, rid, r, j, v);
         }
     }
     template <int MU, int DIR>
@@ -897,7 +841,7 @@ struct TwNb {
                 for (int e = 0; e < 4; e++) v[4 * k + e] = h2_t{C.ch[r][k][2 * e], C.ch[r][k][2 * e + 1]};
             return C.nrm[r];
         } else {
-            return GlobalNb<true>{}.template h2<MU, DIR>(a, rid, r, j, v);
+            return GlobalNb{}.template h2<MU, DIR>(a, rid, r, j, v);
         }
     }
 };
@@ -960,7 +904,7 @@ __global__ void __launch_bounds__(256) dslash_tw_kernel(DslashArgs a)
         if (live) {
             int c[4];
             site_coords(b.g, i, b.P, c);
-            const GlobalNb<true> gnb;
+            const GlobalNb gnb;
             hop_dir<0, SP, LK, NR, DAG>(b, gnb, i, c, rid, acc);
             hop_dir<1, SP, LK, NR, DAG>(b, gnb, i, c, rid, acc);
             hop_dir<2, SP, LK, NR, DAG>(b, gnb, i, c, rid, acc);
