@@ -41,6 +41,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <string>
 #include <vector>
 
@@ -668,8 +669,10 @@ struct BatchSolver {
     bool small() const { return !mixed && p.graphs && !c->timing && cg_small_ok(c->g, nsub); }
 
     // Steps of k iterations of every running RHS in one launch: each stops
-    // where it needs the host (see SmallArgs) or after max_steps.
-    wd_status small_steps(int k, int max_steps)
+    // where it needs the host (see SmallArgs), at limit iterations in all, or
+    // after max_steps.  A session's step is k iterations wherever maxiter lies,
+    // as in step(): the limit is then out of reach.
+    wd_status small_steps(int k, int max_steps, int limit)
     {
         const hipStream_t s = c->stream;
         SmallArgs a;
@@ -687,7 +690,7 @@ struct BatchSolver {
         a.hout = hbuf;
         a.tol2 = p.tol * p.tol;
         a.k = k;
-        a.maxiter = p.maxiter;
+        a.maxiter = limit;
         a.max_steps = max_steps;
         for (size_t b = 0; b < active.size(); b += kSmallBatch) {
             const int n = (int)std::min(active.size() - b, (size_t)kSmallBatch);
@@ -899,7 +902,7 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     WD_TRY(bs.add(phi, nrhs, kappa, nullptr, p.initial_guess ? x : nullptr));
     int it = 0;
     // (every call of small_steps advances each running RHS to maxiter at most)
-    while (bs.running() && p.maxiter > 0 && bs.small()) WD_TRY(bs.small_steps(p.poll, p.maxiter));
+    while (bs.running() && p.maxiter > 0 && bs.small()) WD_TRY(bs.small_steps(p.poll, p.maxiter, p.maxiter));
     while (bs.running() && it < p.maxiter) {
         const int k = std::min(p.poll, p.maxiter - it);
         WD_TRY(bs.step(k));
@@ -986,7 +989,7 @@ extern "C" wd_status wd_session_step(wd_session *s, int k_iters)
     WD_HIP(hipSetDevice(c->device));
     TunedScope tscope{c, c->use_tuned};
     c->use_tuned = s->bs.p.tuned != 0;
-    if (s->bs.small() && s->bs.running()) return s->bs.small_steps(k_iters, 1);
+    if (s->bs.small() && s->bs.running()) return s->bs.small_steps(k_iters, 1, std::numeric_limits<int>::max());
     return s->bs.step(k_iters);
 }
 

@@ -1,0 +1,52 @@
+"""What a call promises beyond its numbers: a refused call leaves its output as
+it was, the two ways a step of iterations can run (graphs = 1 and 0) agree in
+everything a caller sees, a launch stays short, and the device memory held is
+the memory needed."""
+import numpy as np
+import pytest
+
+import lattice_inputs as li
+from gpu_util import dev, empty_like_dev, host, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wd():
+    from paper_1207_2223_amd import wd
+    wd.lib()
+    return wd
+
+
+@pytest.mark.parametrize("eo", [1, 0])
+@pytest.mark.parametrize("maxiter", [13, 16, 3, 0])
+def test_session_at_the_iteration_cap(wd, eo, maxiter):
+    """A step runs all its iterations of every running slot, also where the cap
+    lies inside it; two right-hand sides of different ages."""
+    dims = (4, 4, 4, 4)
+    n = 128 if eo else 256
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.3, seed=84)))
+    B = dev(li.gaussian_spinor(n, seed=85, nrhs=2))
+    got = []
+    for graphs in (1, 0):
+        s = wd.wd_session_create(lat.ctx, 2, wd.solver_params(prec=wd.WD_F64, graphs=graphs, maxiter=maxiter, eo=eo, tol=1e-12))
+        slots = wd.wd_session_add(s, B[:1], [0.14])
+        wd.wd_session_step(s, 8)
+        slots += wd.wd_session_add(s, B[1:], [0.12])
+        steps = 1
+        while any(v == 1 for v in wd.wd_session_poll(s)[0]):
+            wd.wd_session_step(s, 8)
+            steps += 1
+        st = wd.wd_session_poll(s)[1]
+        x = empty_like_dev(B.cpu().numpy())
+        for k, j in enumerate(slots):
+            wd.wd_session_take(s, j, x[k])
+        got.append((steps, [(q["iters"], q["iters_fp64"], q["reliable_updates"], q["status"], q["true_resid"]) for q in st],
+                    host(x).view(np.uint64).tolist()))
+        wd.wd_session_destroy(s)
+    note(f"session cap {maxiter} eo {eo}: {got[0][:2]}")
+    assert got[0][:2] == got[1][:2]
+    assert got[0][2] == got[1][2]
+    assert got[1][1][0][0] == 8 * -(-max(maxiter, 1) // 8)  # whole steps
+    lat.close()
