@@ -231,7 +231,9 @@ extern "C" wd_status wd_point_propagator(wd_ctx *c, double *psi, const int32_t s
     WD_TRY(ws_get(c, "ms_b", sizeof(double) * 12 * col, &vp));
     double *B = (double *)vp;  // Mhat^dag bhat
     // (the twelve columns of a step in one launch; psi, written last, holds
-    // intermediate parity columns)
+    // intermediate parity columns: from here on no argument is refused and no
+    // memory is asked for)
+    WD_TRY(cg_prepare(c, 12, p));
     // bhat_j = b_e + k D_eo b_o
     hipLaunchKernelGGL(k_fill, dim3(nblk(12 * col)), dim3(kB), 0, s, A, 0.0, 12 * col);
     if (par == 0) {

@@ -859,6 +859,21 @@ static wd_status check_params(const wd_solver_params &p)
     return WD_OK;
 }
 
+// The one-shot solver's state, in the context's "cg_" workspaces, reused across
+// calls.
+static wd_status one_shot_init(BatchSolver *bs, wd_ctx *c, int nrhs, const wd_solver_params &p)
+{
+    bs->one_shot = true;
+    return bs->init(c, nrhs, p, "cg_");
+}
+
+wd_status cg_prepare(wd_ctx *c, int nrhs, const wd_solver_params &p)
+{
+    WD_TRY(check_params(p));
+    BatchSolver bs;
+    return one_shot_init(&bs, c, nrhs, p);
+}
+
 }  // namespace wd
 
 using namespace wd;
@@ -894,11 +909,8 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     TunedScope tscope{c, c->use_tuned};
     c->use_tuned = p.tuned != 0;
 
-    // the one-shot solver keeps its state in the context's "cg_" workspaces,
-    // reused across calls
     BatchSolver bs;
-    bs.one_shot = true;
-    WD_TRY(bs.init(c, nrhs, p, "cg_"));
+    WD_TRY(one_shot_init(&bs, c, nrhs, p));
     WD_TRY(bs.add(phi, nrhs, kappa, nullptr, p.initial_guess ? x : nullptr));
     int it = 0;
     // (every call of small_steps advances each running RHS to maxiter at most)

@@ -380,6 +380,9 @@ wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, in
 // out = Mhat^dag in for nrhs canonical FP64 even-parity columns; T: scratch
 // columns of the same size.
 wd_status mhat_dag_apply(wd_ctx *c, double *out, const double *in, double *T, double kappa, int nrhs);
+// Whether wd_cg_solve takes these parameters, and its workspaces for nrhs
+// right-hand sides: after it, that solve is refused no more (solver.hip).
+wd_status cg_prepare(wd_ctx *c, int nrhs, const wd_solver_params &p);
 // full-lattice columns from parity columns, the odd ones times so (pack.hip)
 hipError_t merge_parities(const double *e, const double *o, double so, double *full, int ncol, const Geom &g,
                           hipStream_t s);

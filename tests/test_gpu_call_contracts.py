@@ -18,6 +18,46 @@ def wd():
     return wd
 
 
+@pytest.mark.parametrize("src", [(0, 2, 1, 3), (1, 2, 1, 3)])
+def test_refused_propagator_leaves_its_output(wd, src):
+    """Every parameter the solver checks, both source parities."""
+    import torch
+    dims = (4, 4, 4, 4)
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.3, seed=101)))
+    psi = torch.full((12, li.volume(dims), 4, 3), 7.0 - 3.0j, dtype=torch.complex128, device="cuda")
+    for bad in (dict(tol=0.0), dict(tol=-1.0), dict(maxiter=-1), dict(poll=0), dict(delta=0.0), dict(delta=1.0),
+                dict(prec=0x99), dict(prec=wd.WD_F64 | wd.WD_LINKS_F16), dict(eo=0)):
+        note(f"propagator {src} {bad}")
+        status, _ = wd.wd_point_propagator(lat.ctx, psi, src, 0.11, wd.solver_params(**bad), check=False)
+        assert status == wd.WD_ERR_ARG
+        assert torch.count_nonzero(psi - (7.0 - 3.0j)).item() == 0
+    lat.close()
+
+
+def test_propagator_without_memory_for_its_solve_leaves_its_output(wd):
+    """24^3 x 48 with 12 columns: the solver's state (7 GB in FP16) does not fit
+    the 5 GB that are left, the propagator's own two fields do."""
+    import torch
+    dims = (24, 24, 24, 48)
+    V = li.volume(dims)
+    lat = wd.Lattice(dims)
+    U = torch.zeros((V, 4, 3, 3), dtype=torch.complex128, device="cuda")
+    U[..., 0, 0] = U[..., 1, 1] = U[..., 2, 2] = 1.0
+    lat.gauge_load(U, recon=12)
+    psi = torch.full((12, V, 4, 3), 7.0 - 3.0j, dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    ballast = torch.empty(torch.cuda.mem_get_info()[0] - 5 * 2 ** 30, dtype=torch.uint8, device="cuda")
+    for src in ((0, 0, 0, 0), (1, 0, 0, 0)):
+        status, _ = wd.wd_point_propagator(lat.ctx, psi, src, 0.11, wd.solver_params(prec=wd.WD_F16), check=False)
+        assert status == wd.WD_ERR_OOM
+        assert all(bool((p == 7.0 - 3.0j).all()) for p in psi)
+    del ballast
+    lat.close()
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("eo", [1, 0])
 @pytest.mark.parametrize("maxiter", [13, 16, 3, 0])
 def test_session_at_the_iteration_cap(wd, eo, maxiter):
