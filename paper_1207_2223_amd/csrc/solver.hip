@@ -668,6 +668,11 @@ struct BatchSolver {
     // timing ask for the launches.
     bool small() const { return !mixed && p.graphs && !c->timing && cg_small_ok(c->g, nsub); }
 
+    // Iterations of a launch at most (whole steps; one step at least): at 6 us (2^3
+    // x 4, full lattice) to 18 us (256 even sites) each the host is back after 75
+    // ms whatever maxiter is, and the launch and the wait are nothing beside them.
+    static constexpr int kSmallIters = 4096;
+
     // Steps of k iterations of every running RHS in one launch: each stops
     // where it needs the host (see SmallArgs), at limit iterations in all, or
     // after max_steps.  A session's step is k iterations wherever maxiter lies,
@@ -913,8 +918,9 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     WD_TRY(one_shot_init(&bs, c, nrhs, p));
     WD_TRY(bs.add(phi, nrhs, kappa, nullptr, p.initial_guess ? x : nullptr));
     int it = 0;
-    // (every call of small_steps advances each running RHS to maxiter at most)
-    while (bs.running() && p.maxiter > 0 && bs.small()) WD_TRY(bs.small_steps(p.poll, p.maxiter, p.maxiter));
+    // (every call of small_steps advances each running RHS, to maxiter at most)
+    while (bs.running() && p.maxiter > 0 && bs.small())
+        WD_TRY(bs.small_steps(p.poll, std::max(1, BatchSolver::kSmallIters / p.poll), p.maxiter));
     while (bs.running() && it < p.maxiter) {
         const int k = std::min(p.poll, p.maxiter - it);
         WD_TRY(bs.step(k));

@@ -90,3 +90,41 @@ def test_session_at_the_iteration_cap(wd, eo, maxiter):
     assert got[0][2] == got[1][2]
     assert got[1][1][0][0] == 8 * -(-max(maxiter, 1) // 8)  # whole steps
     lat.close()
+
+
+def singular(wd, dims, eo):
+    """U = 1 at kappa = 1/8: a zero mode, so that a source with a constant part
+    has no solution and CG runs to its cap."""
+    V = li.volume(dims)
+    U = np.zeros((V, 4, 3, 3), complex)
+    U[..., range(3), range(3)] = 1.0
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(U))
+    return lat, li.gaussian_spinor(V // 2 if eo else V, seed=86) + 1.0
+
+
+@pytest.mark.parametrize("eo", [1, 0])
+def test_one_launch_runs_a_bounded_number_of_iterations(wd, eo):
+    """The host is back after some thousand iterations whatever the cap: the
+    launches of a solve that does not converge, and the same result as a launch
+    a kernel gives."""
+    from torch.profiler import ProfilerActivity, profile
+    import torch
+    lat, b = singular(wd, (4, 4, 4, 4), eo)
+    B = dev(b[None])
+    x = empty_like_dev(b[None])
+    res = []
+    for graphs, cap in ((1, 20000), (1, 4500), (0, 4500)):
+        p = wd.solver_params(tol=1e-10, maxiter=cap, graphs=graphs, eo=eo)
+        if graphs and cap == 20000:
+            with profile(activities=[ProfilerActivity.CUDA]) as prof:
+                st, stats = lat.cg_solve(x, B, [0.125], p)
+                torch.cuda.synchronize()
+            launches = sum(e.count for e in prof.key_averages() if "k_cg_small" in e.key)
+            note(f"eo {eo}: {stats[0]['iters']} iterations in {launches} launches, status {st}")
+            assert stats[0]["iters"] == cap and launches >= 4
+        else:
+            st, stats = lat.cg_solve(x, B, [0.125], p)
+            res.append((st, stats[0]["iters"], stats[0]["reliable_updates"], host(x).view(np.uint64).tolist()))
+    assert res[0] == res[1]
+    lat.close()
