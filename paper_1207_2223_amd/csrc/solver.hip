@@ -672,6 +672,8 @@ struct BatchSolver {
     // x 4, full lattice) to 18 us (256 even sites) each the host is back after 75
     // ms whatever maxiter is, and the launch and the wait are nothing beside them.
     static constexpr int kSmallIters = 4096;
+    // steps of a launch (WD_SOLVER_TRACE prints after every step)
+    int small_max_steps() const { return trace ? 1 : std::max(1, kSmallIters / p.poll); }
 
     // Steps of k iterations of every running RHS in one launch: each stops
     // where it needs the host (see SmallArgs), at limit iterations in all, or
@@ -920,7 +922,7 @@ extern "C" wd_status wd_cg_solve(wd_ctx *c, double *x, const double *phi, int nr
     int it = 0;
     // (every call of small_steps advances each running RHS, to maxiter at most)
     while (bs.running() && p.maxiter > 0 && bs.small())
-        WD_TRY(bs.small_steps(p.poll, std::max(1, BatchSolver::kSmallIters / p.poll), p.maxiter));
+        WD_TRY(bs.small_steps(p.poll, bs.small_max_steps(), p.maxiter));
     while (bs.running() && it < p.maxiter) {
         const int k = std::min(p.poll, p.maxiter - it);
         WD_TRY(bs.step(k));

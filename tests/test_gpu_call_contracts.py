@@ -92,6 +92,22 @@ def test_session_at_the_iteration_cap(wd, eo, maxiter):
     lat.close()
 
 
+def test_trace_prints_every_poll(wd, monkeypatch, capfd):
+    dims = (4, 4, 4, 4)
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.3, seed=84)))
+    B = dev(li.gaussian_spinor(128, seed=85, nrhs=2))
+    monkeypatch.setenv("WD_SOLVER_TRACE", "1")
+    lines = []
+    for graphs in (1, 0):
+        capfd.readouterr()
+        lat.cg_solve(empty_like_dev(B.cpu().numpy()), B, [0.14, 0.12], wd.solver_params(tol=1e-10, graphs=graphs))
+        lines.append([q for q in capfd.readouterr().err.splitlines() if q.startswith("[wd cg]")])
+    assert len(lines[1]) > 8
+    assert lines[0] == lines[1]
+    lat.close()
+
+
 def singular(wd, dims, eo):
     """U = 1 at kappa = 1/8: a zero mode, so that a source with a constant part
     has no solution and CG runs to its cap."""
