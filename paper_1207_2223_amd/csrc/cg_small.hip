@@ -15,6 +15,12 @@
 // as much again if each half loaded all of them, hence load_link_halves.  Full
 // 4^4 solve to 1e-12, 168 iterations: 6.69 ms with the general path, 39.8 us an
 // iteration; 1.5 ms in this kernel.
+//
+// A launch takes as many right-hand sides as there are CUs (the LDS holds one
+// work-group a CU; the id lists, 2 KB, are kernel arguments).  Even-odd 4^4
+// solves to 1e-12 of 256 and 1000 right-hand sides: 4.4 and 13.0 ms with the
+// general path, 5.1 and 20.4 with launches of 32 one after the other, 0.90 and
+// 3.7 with 256; 2^3 x 4 with 1000: 9.0, 24.0 and 3.4.
 #include <cmath>
 
 #include "half_spinor.h"
@@ -70,6 +76,8 @@ __device__ __forceinline__ double sum_leaves(const double *leaf, int n)
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
+
+static_assert(sizeof(SmallArgs) <= 4096, "kernel arguments");
 
 // One work-group per right-hand side, 64 threads per 32 sites (Vh sites, or 2
 // Vh on the full lattice).

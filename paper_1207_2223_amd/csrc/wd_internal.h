@@ -158,7 +158,7 @@ hipError_t op_launch_i16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, i
 // listed right-hand side runs steps of k iterations until its |r|^2 is not
 // above tol2 * bb, not finite, or it reaches maxiter, at most max_steps.
 constexpr int kSmallSites = 256;  // sites of a vector
-constexpr int kSmallBatch = 32;   // right-hand sides of a launch
+constexpr int kSmallBatch = 256;  // right-hand sides of a launch (see cg_small.hip)
 struct SmallArgs {
     Geom g;
     const char *links = nullptr;

@@ -144,3 +144,32 @@ def test_one_launch_runs_a_bounded_number_of_iterations(wd, eo):
             res.append((st, stats[0]["iters"], stats[0]["reliable_updates"], host(x).view(np.uint64).tolist()))
     assert res[0] == res[1]
     lat.close()
+
+
+@pytest.mark.parametrize("eo,dims", [(1, (2, 2, 2, 4)), (1, (4, 4, 4, 8)), (0, (4, 4, 4, 4))])
+def test_many_right_hand_sides_on_a_small_lattice(wd, eo, dims):
+    """More right-hand sides than a launch holds, in steps of one launch per 256:
+    the bits of the launched kernels, and not slower than those (best of three)."""
+    import time
+    import torch
+    V, n = li.volume(dims), 600
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.random_su3_field(dims, 0.4, seed=88)))
+    B = li.gaussian_spinor(V // 2 if eo else V, seed=89, nrhs=n)
+    b, x = dev(B), empty_like_dev(B)
+    kap = np.linspace(0.11, 0.13, n)
+    got, best = [], []
+    for graphs in (1, 0):
+        p = wd.solver_params(tol=1e-11, graphs=graphs, eo=eo)
+        ts = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            st, stats = lat.cg_solve(x, b, kap, p)
+            ts.append(time.perf_counter() - t)
+        got.append((st, [(s["iters"], s["reliable_updates"], s["true_resid"]) for s in stats], host(x).view(np.uint64)))
+        best.append(min(ts[1:]))
+    note(f"{n} RHS {dims} eo {eo}: one launch {best[0] * 1e3:.2f} ms, launches {best[1] * 1e3:.2f} ms")
+    assert got[0][:2] == got[1][:2] and np.array_equal(got[0][2], got[1][2])
+    assert best[0] <= 1.1 * best[1]
+    lat.close()
