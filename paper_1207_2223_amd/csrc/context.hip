@@ -157,12 +157,23 @@ static TuneCfg untuned_cfg(const wd_ctx *c, const Sweep &sw)
         t.remap = 6;
         t.occ = 4;
     } else if (slab_order_ok(c->g, 32, 2)) {
-        // a z slab per XCD: 24^4, 6 RHS 182 / 200 / 224 -> 175 / 195 / 216; two RHS a
-        // lane where that leaves no slot empty: 24^3 x 48, 8 RHS 453 / 504 / 563
-        // -> 431 / 498 / 552 (24^4, 6 RHS: 197 / 231 / 257)
-        t.remap = 2;
-        t.rl = 2;
-        if (sw.nact % 4 == 0) t.nr = 2;
+        // a z slab per XCD, two lanes a site: 24^4, 6 RHS 182 / 200 / 224 -> 175 /
+        // 195 / 216; two RHS a lane where that leaves no slot empty: 24^3 x 48, 8
+        // RHS 453 / 504 / 563 -> 431 / 498 / 552 (24^4, 6 RHS: 197 / 231 / 257).
+        // An odd batch leaves a slot of every site empty, which only a large one
+        // of seven or more makes up for (plain, mean of D_eo and D_oe^dag; z slabs
+        // against dispatch order with four work-groups a CU: 24^4, 7 RHS [1.2 M]
+        // 249, 254, 24^3 x 48 475, 488; but 5 RHS 188, 177 and 368, 346, 24^4, 3
+        // RHS 125, 108, 16 x 12 x 40 x 18, 9 RHS [622 k] 122, 119); small ones
+        // without the cap (16 x 12 x 16 x 18, 7 RHS [194 k] 35.5, 33.4, without
+        // 31.8; 9 RHS [249 k] 42.1, 41.1, 41.2)
+        if (sw.nact % 2 == 0 || (sw.nact >= 7 && work >= 800000)) {
+            t.remap = 2;
+            t.rl = 2;
+            if (sw.nact % 4 == 0) t.nr = 2;
+        } else if (work >= 250000) {
+            t.occ = 4;
+        }
     } else if (large) {
         t.nr = 2;  // 24^3 x 48, 8 RHS: 514 / 577 / 659 -> 452 / 535 / 627
     }
