@@ -915,11 +915,11 @@ size_t wd_bytes_required(const int32_t dims[4], int nrhs, const wd_solver_params
     size_t links = (144 + 48 + 24 + 72) * 4 * (size_t)V;
     const int sp = p->prec_sloppy & 0xf;
     const size_t nsub = p->eo ? 1 : 2;
-    // FP64: b, x, r, p, Ap, a full-size temporary and a one-parity temporary;
-    // a mixed even-odd solve also holds the ring of sloppy search directions
-    // (an FP64 solve advances its solution every iteration)
+    // FP64: b, x, r, p, a full-size temporary and a one-parity temporary, on the
+    // full lattice A p too; a mixed even-odd solve also holds the ring of sloppy
+    // search directions (an FP64 solve advances its solution every iteration)
     const size_t ring = (p->eo && sp != WD_F64) ? (size_t)(kMaxRing - 1) : 0;
-    size_t f64 = (6 * nsub + 1) * 192 * Vh;
+    size_t f64 = ((p->eo ? 5 : 6) * nsub + 1) * 192 * Vh;
     size_t sl = 0;
     if (sp != WD_F64)
         sl = (4 + ring) * spinor_site_bytes(sp == WD_F32 ? SP_F32 : SP_F16) * Vh * nsub + 96 * Vh * nsub;

@@ -92,7 +92,9 @@ struct BatchSolver {
     int cap = 0, sp = 0, lk = 0, xp = 0, nsub = 1, Vh = 0;
     bool mixed = false;
     int pstride = 0, nw1 = 0, nwF = 0, nwD = 0;
-    Field b64, x64, r64, to64, te64, Ap64, p64, ps, rs, t2s, tos, xs;
+    Field b64, x64, r64, to64, te64, p64;
+    Field Ap64;  // A p of the full-lattice iteration (not allocated with eo)
+    Field ps, rs, t2s, tos, xs;
     Lane lane_s{}, lane_d{};
     double *bb = nullptr, *rr = nullptr, *alpha = nullptr, *beta = nullptr, *dre = nullptr, *dim = nullptr;
     double *coef1 = nullptr, *coef2 = nullptr, *partial = nullptr, *partial2 = nullptr;
@@ -183,7 +185,7 @@ struct BatchSolver {
         WD_TRY(alloc_field(c, nm("r"), SP_F64, nsub, cap, &r64));
         WD_TRY(alloc_field(c, nm("to"), SP_F64, 1, cap, &to64));
         WD_TRY(alloc_field(c, nm("te"), SP_F64, nsub, cap, &te64));
-        WD_TRY(alloc_field(c, nm("ap"), SP_F64, nsub, cap, &Ap64));
+        if (!p.eo) WD_TRY(alloc_field(c, nm("ap"), SP_F64, nsub, cap, &Ap64));
         WD_TRY(alloc_field(c, nm("p"), SP_F64, nsub, cap, &p64));
         lane_d = Lane{SP_F64, c->lk64, SP_F64, p64, r64, te64, to64, x64, false, {p64}};
         if (mixed) {
@@ -196,7 +198,7 @@ struct BatchSolver {
         }
         // the ring slots 1 .. kRing-1 of the sloppy lane; an FP64 solve keeps
         // a ring of one (x advanced every iteration), which holds its memory
-        // per RHS at seven FP64 vectors for serving
+        // per RHS at six FP64 vectors for serving
         if (p.eo && mixed)
             for (int j = 1; j < kRing; j++) {
                 Field f;
@@ -247,8 +249,8 @@ struct BatchSolver {
                                      {nm("r"), (size_t)r64.rs, 0},
                                      {nm("to"), (size_t)to64.rs, 0},
                                      {nm("te"), (size_t)te64.rs, 0},
-                                     {nm("ap"), (size_t)Ap64.rs, 0},
                                      {nm("p"), (size_t)p64.rs, 0}};
+        if (!p.eo) sp_list.push_back({nm("ap"), (size_t)Ap64.rs, 0});
         if (mixed)
             for (auto f : {std::make_pair("ps", &ps), std::make_pair("rs", &rs), std::make_pair("t2s", &t2s),
                            std::make_pair("tos", &tos), std::make_pair("xs", &xs)})
@@ -324,13 +326,11 @@ struct BatchSolver {
         return WD_OK;
     }
 
-    // The last sweeps of A in as out = A in, or as the true residual r64 = b64 -
-    // A in with the partials of |r64|^2 (nwD of them).
-    enum Last { APPLY, RESID };
-
-    // A in (FP64) for the listed RHS, temporaries to64, te64; norm: the partials
-    // of |M in|^2 (full-lattice solver).
-    wd_status apply_A(const Field &in, const Field &out, const int *ids, int n, bool norm, Last last)
+    // The FP64 sweeps of A in for the listed RHS, temporaries to64, te64.  Without
+    // out the last ones form the true residual r64 = b64 - A in and the partials
+    // of |r64|^2 (nwD of them); with it (full lattice only: the even-odd iteration
+    // runs its own sweeps) out = A in and the partials of |M in|^2.
+    wd_status apply_A(const Field &in, const Field *out, const int *ids, int n)
     {
         Sweep sw;
         sw.sp = SP_F64;
@@ -345,32 +345,26 @@ struct BatchSolver {
             WD_TRY(run_sweep(c, sw, nullptr));
             sw.P = 1; sw.dag = 1; sw.epi = EPI_PLAIN; sw.in = te64; sw.out = to64;
             WD_TRY(run_sweep(c, sw, nullptr));
-            sw.P = 0; sw.in = to64; sw.x = te64;
-            if (last == RESID) {
-                sw.epi = EPI_CGUPD; sw.r = r64; sw.rsrc = b64.base;
-                sw.partial = partial; sw.pstride = pstride; sw.pw_off = 0;
-            } else {
-                sw.epi = EPI_XPAY; sw.out = out;
-            }
+            sw.P = 0; sw.epi = EPI_CGUPD; sw.in = to64; sw.x = te64;
+            sw.r = r64; sw.rsrc = b64.base;
+            sw.partial = partial; sw.pstride = pstride; sw.pw_off = 0;
             WD_TRY(run_sweep(c, sw, nullptr));
         } else {
-            const Field &T = te64;
             sw.coef = coef1;
             sw.pstride = pstride;
             for (int pass = 0; pass < 2; pass++) {
-                const Field &src = pass ? T : in;
-                const Field &dst = pass ? out : T;
-                const bool res = pass == 1 && last == RESID;
+                const Field &src = pass ? te64 : in;
+                const bool res = pass == 1 && !out;
                 sw.dag = pass;
                 sw.epi = res ? EPI_CGUPD : EPI_XPAY;
                 for (int P = 0; P < 2; P++) {
                     sw.P = P;
                     sw.in = sub_view(src, 1 - P);
                     sw.x = sub_view(src, P);
-                    sw.out = sub_view(dst, P);
+                    if (!res) sw.out = sub_view(pass ? *out : te64, P);
                     sw.r = sub_view(r64, P);
                     sw.rsrc = res ? sub_view(b64, P).base : nullptr;
-                    sw.partial = ((norm && pass == 0) || res) ? partial : nullptr;
+                    sw.partial = ((out && pass == 0) || res) ? partial : nullptr;
                     sw.pw_off = P * nw1;
                     WD_TRY(run_sweep(c, sw, nullptr));
                 }
@@ -450,7 +444,7 @@ struct BatchSolver {
                 HIPCHK(blas_p_update_ring(&L.Pr[j], 1, L.Pr[j + 1], L.R, bf, beta, false, L.X, ahist, cap, Vh, ids,
                                           n, s));
         } else {
-            WD_TRY(apply_A(L.P, Ap64, ids, n, true, APPLY));
+            WD_TRY(apply_A(L.P, &Ap64, ids, n));
             HIPCHK(blas_finalize(partial, pstride, nwD, ids, n, FIN_ALPHA, rr, alpha, beta, nullptr, nullptr, s));
             HIPCHK(blas_cg_update(L.X, L.P, L.R, Ap64, alpha, Vh, ids, n, partial, pstride, s));
             HIPCHK(blas_finalize(partial, pstride, nwF, ids, n, FIN_BETA, rr, alpha, beta, nullptr,
@@ -510,7 +504,7 @@ struct BatchSolver {
             HIPCHK(blas_norm(b64, Vh, lst, n, partial, pstride, s));
             HIPCHK(blas_finalize(partial, pstride, nwF, lst, n, FIN_STORE, rr, alpha, beta, bb, hbb, s));
             WD_TRY(pack(x0, x64));
-            WD_TRY(apply_A(x64, Ap64, lst, n, false, RESID));
+            WD_TRY(apply_A(x64, nullptr, lst, n));
             HIPCHK(blas_finalize(partial, pstride, nwD, lst, n, FIN_RR, rr, alpha, beta, nullptr, hbuf, s));
             HIPCHK(blas_cg_init(false, b64, x64, r64, rs, xs, lane_s.P, Vh, lst, n, partial, pstride, s));
         } else {
@@ -571,7 +565,7 @@ struct BatchSolver {
         WD_TRY(set_list(ids, lst));
         const int n = (int)ids.size();
         HIPCHK(blas_ru_begin(L.P, L.R, x64, L.sloppy ? &L.X : nullptr, rr, rr_s, Vh, lst, n, s));
-        WD_TRY(apply_A(x64, Ap64, lst, n, false, RESID));
+        WD_TRY(apply_A(x64, nullptr, lst, n));
         // (|r|^2's nwD partials are followed by Re <r, p>'s, so one launch sums all)
         double *const pre = partial + nwD;
         HIPCHK(blas_ru_mid(r64, L.R, L.sloppy, L.P, Vh, lst, n, pre, partial2, pstride, s));

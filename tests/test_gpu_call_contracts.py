@@ -146,6 +146,41 @@ def test_one_launch_runs_a_bounded_number_of_iterations(wd, eo):
     lat.close()
 
 
+def held(f):
+    """Device bytes that f() leaves allocated outside torch's pool."""
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    keep = f()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0], keep
+
+
+@pytest.mark.parametrize("eo,prec,vectors", [(1, "f64", 6), (0, "f64", 13), (1, "f16", 6)])
+def test_session_holds_the_vectors_it_uses(wd, eo, prec, vectors):
+    """FP64 vectors of a parity per slot: b, x, r, p and two temporaries (the
+    full lattice, two parities each: A p too, one temporary of one parity), and
+    in FP16 twelve vectors of 52 bytes and the increment of 96.  The charge is
+    what the session holds."""
+    dims = (16, 16, 16, 16)
+    code = {"f64": wd.WD_F64, "f16": wd.WD_F16}[prec]
+    lat = wd.Lattice(dims)
+    lat.gauge_load(dev(li.unit_field(dims)))
+    p = wd.solver_params(prec=code, eo=eo)
+    n, stride = 64, (li.volume(dims) // 2 + 63) // 64 * 64 + 592
+    need = n * stride * (192 * vectors + (11 * 52 + 96 if prec == "f16" else 0))
+    got, s = held(lambda: wd.wd_session_create(lat.ctx, n, p))
+    charge = wd.wd_session_bytes(dims, n, p)
+    note(f"session eo {eo} {prec}: holds {got / 2 ** 20:.1f} MiB, needs {need / 2 ** 20:.1f}, charged {charge / 2 ** 20:.1f}")
+    # norm partials and scalars: about 1 % of a vector a slot; allocations are whole pages of 2 MiB
+    slack = 0.02 * need + 40 * 2 ** 21
+    assert abs(charge - need) <= 0.02 * need
+    assert got <= need + slack
+    wd.wd_session_destroy(s)
+    lat.close()
+
+
 @pytest.mark.parametrize("eo,dims", [(1, (2, 2, 2, 4)), (1, (4, 4, 4, 8)), (0, (4, 4, 4, 4))])
 def test_many_right_hand_sides_on_a_small_lattice(wd, eo, dims):
     """More right-hand sides than a launch holds, in steps of one launch per 256:
