@@ -804,10 +804,9 @@ wd_status wd_mdagm(wd_ctx *c, double *out, const double *in, double kappa, int e
     if (!c->have_gauge) return set_error(WD_ERR_STATE, "no gauge field loaded");
     if (!std::isfinite(kappa)) return set_error(WD_ERR_ARG, "kappa not finite");
     WD_HIP(hipSetDevice(c->device));
-    const int nsub = eo ? 1 : 2;
     Field T, B;
-    WD_TRY(alloc_field(c, "mdm_t", SP_F64, nsub, 1, &T));
-    WD_TRY(alloc_field(c, "mdm_b", SP_F64, nsub, 1, &B));
+    WD_TRY(alloc_field(c, "mdm_t", SP_F64, eo ? 1 : 2, 1, &T));
+    if (eo) WD_TRY(alloc_field(c, "mdm_b", SP_F64, 1, 1, &B));
     return mdagm_apply(c, out, in, kappa, eo, T, B);
 }
 

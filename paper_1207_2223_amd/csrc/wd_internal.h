@@ -374,8 +374,8 @@ double sweep_bytes(const wd_ctx *c, const Sweep &sw);
 wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs);
 bool op_reads_canonical(const wd_ctx *c, int sp, int np, const void *in, const void *out, size_t in_bytes,
                         size_t out_bytes);
-// M^dag M or Mhat^dag Mhat of a canonical FP64 field through FP64 buffers of
-// one (eo) or two subfields, T and B.
+// M^dag M or Mhat^dag Mhat of a canonical FP64 field through FP64 buffers: T of
+// one subfield (eo) or two, and B of one (eo only).
 wd_status mdagm_apply(wd_ctx *c, double *out, const double *in, double kappa, int eo, const Field &T, const Field &B);
 // out = Mhat^dag in for nrhs canonical FP64 even-parity columns; T: scratch
 // columns of the same size.

@@ -181,6 +181,24 @@ def test_session_holds_the_vectors_it_uses(wd, eo, prec, vectors):
     lat.close()
 
 
+@pytest.mark.parametrize("eo,fields", [(0, 2), (1, 2)])
+def test_normal_operator_holds_the_temporaries_it_uses(wd, eo, fields):
+    """Even-odd: T and B of one parity; the full lattice: T of two."""
+    import torch
+    dims = (32, 32, 32, 16)
+    V = li.volume(dims)
+    lat = wd.Lattice(dims)
+    U = torch.zeros((V, 4, 3, 3), dtype=torch.complex128, device="cuda")
+    U[..., 0, 0] = U[..., 1, 1] = U[..., 2, 2] = 1.0
+    lat.gauge_load(U, recon=12)
+    b = torch.ones((V // 2 if eo else V, 4, 3), dtype=torch.complex128, device="cuda")
+    out = torch.empty_like(b)
+    got, _ = held(lambda: lat.mdagm(out, b, 0.1, eo=eo))
+    note(f"normal operator eo {eo}: holds {got / 2 ** 20:.1f} MiB")
+    assert got <= 1.02 * fields * (V // 2) * 192 + 8 * 2 ** 21
+    lat.close()
+
+
 @pytest.mark.parametrize("eo,dims", [(1, (2, 2, 2, 4)), (1, (4, 4, 4, 8)), (0, (4, 4, 4, 4))])
 def test_many_right_hand_sides_on_a_small_lattice(wd, eo, dims):
     """More right-hand sides than a launch holds, in steps of one launch per 256:
