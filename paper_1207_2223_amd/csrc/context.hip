@@ -364,7 +364,9 @@ wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs)
     // the last-level cache a repeated call finds them there and the hint only
     // hurts (16^3 x 32, 101 MB: Mhat^dag Mhat 68 against 77 us); above it the
     // hint leaves the L2 to the spinors (24^3 x 48, 254 MB: 372 against 400).
-    const bool nt = (double)c->Vh * o.np * 8.0 * (double)link_bytes(lk) > 180e6;
+    // (FP32 18-real, FP16 and the int16 sweeps' links have no such variant)
+    const bool nt = (double)c->Vh * o.np * 8.0 * (double)link_bytes(lk) > 180e6 && sp != SP_I16 && lnt_variant(lk) >= 0;
+    const int lk_run = nt ? lnt_variant(lk) : lk;
     const int block = 64;
     const long long tiles = (c->Vh + block - 1) / block * o.np;
     if (tiles > 0x7fffffffLL || nrhs > 65535) return set_error(WD_ERR_ARG, "grid too large");
@@ -373,16 +375,16 @@ wd_status op_sweep(wd_ctx *c, OpArgs o, int sp, int lk, int dag, int nrhs)
     if (c->timing) WD_TRY(timing_begin(c, &e0, &e1));
     hipError_t e = hipErrorInvalidValue;
     switch (sp) {
-    case SP_F64: e = op_launch_f64(o, lk, nt, dag, grid, block, c->stream); break;
-    case SP_F32: e = op_launch_f32(o, lk, nt, dag, grid, block, c->stream); break;
-    case SP_F16: e = op_launch_f16(o, lk, nt, dag, grid, block, c->stream); break;
-    case SP_I16: e = op_launch_i16(o, lk, nt, dag, grid, block, c->stream); break;
+    case SP_F64: e = op_launch_f64(o, lk_run, dag, grid, block, c->stream); break;
+    case SP_F32: e = op_launch_f32(o, lk_run, dag, grid, block, c->stream); break;
+    case SP_F16: e = op_launch_f16(o, lk_run, dag, grid, block, c->stream); break;
+    case SP_I16: e = op_launch_i16(o, lk_run, dag, grid, block, c->stream); break;
     }
     if (e != hipSuccess)
-        return set_error(WD_ERR_HIP, "operator sweep launch (sp %d lk %d): %s", sp, lk, hipGetErrorString(e));
+        return set_error(WD_ERR_HIP, "operator sweep launch (sp %d lk %d): %s", sp, lk_run, hipGetErrorString(e));
     if (c->timing) {
         char name[96];
-        snprintf(name, sizeof(name), "dslash_op_kernel<%d, %d, %s, %s>", sp, lk, dag ? "true" : "false",
+        snprintf(name, sizeof(name), "dslash_op_kernel<%d, %d, %s, %s>", sp, lk_run, dag ? "true" : "false",
                  o.incanon ? "true" : "false");
         const double units = (double)c->Vh * o.np * nrhs;
         const double sb = (double)spinor_site_bytes(sp), io = (o.incanon ? 192.0 : sb) + (o.outcanon ? 192.0 : sb) +

@@ -205,9 +205,7 @@ __global__ void __launch_bounds__(256) dslash_op_kernel(OpArgs o)
     if (o.incanon) { WD_OP_ONE(SP_, LK_, false, true) }                                           \
     WD_OP_ONE(SP_, LK_, false, false)
 
-// LKN_: the links read non-temporally (nt, the host's rule in op_sweep).
-#define WD_OP_CASE(SP_, LK_, LKN_)                                                                \
-    if (lk == LK_ && nt) { WD_OP_LK(SP_, LKN_) }                                                  \
+#define WD_OP_CASE(SP_, LK_)                                                                      \
     if (lk == LK_) { WD_OP_LK(SP_, LK_) }
 
 }  // namespace wd

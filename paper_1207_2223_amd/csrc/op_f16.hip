@@ -3,12 +3,14 @@
 
 namespace wd {
 
-hipError_t op_launch_f16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s)
+hipError_t op_launch_f16(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s)
 {
-    WD_OP_CASE(SP_F16, LK_F32_12, LK_F32_12N)
-    WD_OP_CASE(SP_F16, LK_F32_18, LK_F32_18)
-    WD_OP_CASE(SP_F16, LK_F32_8, LK_F32_8N)
-    WD_OP_CASE(SP_F16, LK_F16_12, LK_F16_12)
+    WD_OP_CASE(SP_F16, LK_F32_12)
+    WD_OP_CASE(SP_F16, LK_F32_12N)
+    WD_OP_CASE(SP_F16, LK_F32_18)
+    WD_OP_CASE(SP_F16, LK_F32_8)
+    WD_OP_CASE(SP_F16, LK_F32_8N)
+    WD_OP_CASE(SP_F16, LK_F16_12)
     return hipErrorInvalidValue;
 }
 

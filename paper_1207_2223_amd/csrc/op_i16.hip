@@ -3,10 +3,10 @@
 
 namespace wd {
 
-hipError_t op_launch_i16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s)
+hipError_t op_launch_i16(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s)
 {
-    WD_OP_CASE(SP_I16, LK_F32_12, LK_F32_12)
-    WD_OP_CASE(SP_I16, LK_F16_12, LK_F16_12)
+    WD_OP_CASE(SP_I16, LK_F32_12)
+    WD_OP_CASE(SP_I16, LK_F16_12)
     return hipErrorInvalidValue;
 }
 

@@ -98,11 +98,18 @@ struct TuneCfg {
     int lnt = 0;  // 1: links loaded non-temporally (FP32 12/8-real, FP64 12-real; register-tiled, rl 1, nr 1-2)
 };
 // Whether a shape of a sweep with links lk may take lnt = 1, and the
-// non-temporal launch variant of a link format (-1: none).
+// non-temporal launch variant of a link format (-1: none; FP64 18-real: of the
+// operator sweeps only).
 bool lnt_ok(int sp, int lk, const TuneCfg &t);
 inline int lnt_variant(int lk)
 {
-    return lk == LK_F32_12 ? LK_F32_12N : (lk == LK_F64_12 ? LK_F64_12N : (lk == LK_F32_8 ? LK_F32_8N : -1));
+    switch (lk) {
+    case LK_F32_12: return LK_F32_12N;
+    case LK_F32_8: return LK_F32_8N;
+    case LK_F64_12: return LK_F64_12N;
+    case LK_F64_18: return LK_F64_18N;
+    default: return -1;
+    }
 }
 
 // LDS per CU on gfx950, and the dynamic LDS per work-group that lets at most
@@ -149,10 +156,11 @@ struct OpArgs {
     char *out = nullptr;
     long long out_rs = 0, out_ss = 0;
 };
-hipError_t op_launch_f64(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
-hipError_t op_launch_f32(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
-hipError_t op_launch_f16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
-hipError_t op_launch_i16(const OpArgs &o, int lk, bool nt, int dag, dim3 grid, int block, hipStream_t s);
+// lk: the link format, or its non-temporal launch variant
+hipError_t op_launch_f64(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_f32(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_f16(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s);
+hipError_t op_launch_i16(const OpArgs &o, int lk, int dag, dim3 grid, int block, hipStream_t s);
 
 // CG steps of small lattices in one launch (cg_small.hip): one work-group per
 // listed right-hand side runs steps of k iterations until its |r|^2 is not

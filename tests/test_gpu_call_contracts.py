@@ -199,6 +199,29 @@ def test_normal_operator_holds_the_temporaries_it_uses(wd, eo, fields):
     lat.close()
 
 
+def test_timing_names_the_instance_that_ran(wd):
+    """Operator sweeps over links beyond the last-level cache run the instance
+    that reads them non-temporally: link format 6 instead of 2 (FP32 12-real),
+    9 instead of 0 (FP64 18-real)."""
+    import torch
+    for dims, lk32, lk64 in (((32, 32, 32, 32), 6, 9), ((8, 8, 8, 8), 2, 0)):
+        V = li.volume(dims)
+        lat = wd.Lattice(dims)
+        U = torch.zeros((V, 4, 3, 3), dtype=torch.complex128, device="cuda")
+        U[..., 0, 0] = U[..., 1, 1] = U[..., 2, 2] = 1.0
+        lat.gauge_load(U, recon=18)
+        b = torch.ones((V // 2, 4, 3), dtype=torch.complex128, device="cuda")
+        out = torch.empty_like(b)
+        wd.wd_timing_enable(lat.ctx, True)
+        lat.dslash(out, b, wd.WD_EVEN, 0, wd.WD_F32)
+        lat.dslash(out, b, wd.WD_EVEN, 1, wd.WD_F64)
+        names = sorted(wd.wd_timing_report(lat.ctx))
+        note(f"timing {dims}: {names}")
+        canon = "false" if dims[0] == 32 else "true"
+        assert names == [f"dslash_op_kernel<0, {lk64}, true, true>", f"dslash_op_kernel<1, {lk32}, false, {canon}>"]
+        lat.close()
+
+
 @pytest.mark.parametrize("eo,dims", [(1, (2, 2, 2, 4)), (1, (4, 4, 4, 8)), (0, (4, 4, 4, 4))])
 def test_many_right_hand_sides_on_a_small_lattice(wd, eo, dims):
     """More right-hand sides than a launch holds, in steps of one launch per 256:
