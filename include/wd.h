@@ -96,8 +96,9 @@ typedef struct {
     int poll;         /* iterations between host checks of the residual norms       */
     int tuned;        /* 1: use autotuned launch shapes (wd_tune), 0: defaults      */
     int graphs;       /* 1: run the poll iterations of a step as one captured HIP   */
-                      /* graph, replayed while the active set is unchanged; 0:    */
-                      /* launch each kernel (same results bit for bit)            */
+                      /* graph, replayed while the active set is unchanged, or    */
+                      /* (FP64, at most 256 sites) as one kernel; 0: launch each  */
+                      /* kernel (same results bit for bit)                        */
     int initial_guess; /* wd_cg_solve: 1: x holds the starting vectors on entry  */
                       /* (r0 = b - A x in FP64); 0: x0 = 0 (x is output only)     */
 } wd_solver_params;
@@ -177,15 +178,15 @@ wd_status wd_mdagm(wd_ctx *c, double *out, const double *in, double kappa, int e
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * normal operator as wd_mdagm -- same arguments, same kernels, the same bits
- * -- with its packed operand, temporaries and device scalars in a fixed
- * device array of 64 MiB per GPU (held from the first wd_create on that GPU
- * until the process ends) instead of context workspaces.  The call allocates
- * nothing and copies nothing between host and device.  Lattices whose
- * operator needs more than the 64 MiB (about Vh <= 87000 for eo = 1, Vh <=
- * 58000 for eo = 0; e.g. 16^3 x 32 even-odd fits, its full lattice does not)
- * are refused with WD_ERR_ARG before any work is issued.  Every call on one
- * GPU uses that GPU's array: calls that overlap on one GPU (other streams or
- * threads) race and must be serialised by the caller. */
+ * -- with its temporaries in a fixed device array of 64 MiB per GPU (held
+ * from the first wd_create on that GPU until the process ends) instead of
+ * context workspaces.  The call allocates
+ * nothing and copies nothing between host and device.  Lattices whose fields
+ * (four of a parity for eo = 1, six for eo = 0) exceed the 64 MiB (Vh above
+ * about 87000 or 58000; e.g. 16^3 x 32 even-odd fits, its full lattice does
+ * not) are refused with WD_ERR_ARG before any work is issued.  Every call on
+ * one GPU uses that GPU's array: calls that overlap on one GPU (other streams
+ * or threads) race and must be serialised by the caller. */
 wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, double kappa, int eo);
 
 /* Solve A x_j = phi_j for nrhs right-hand sides at once (eq. 3: the inverse

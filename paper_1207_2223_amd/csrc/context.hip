@@ -342,11 +342,12 @@ wd_status run_sweep(wd_ctx *c, const Sweep &sw, const TuneCfg *cfg)
 // (its neighbours at 192-byte strides) or a packed copy.  FP64 reads it where
 // it lies at all sizes: D_eo, 18-real links, packed and here: 16^3 x 32 30.3 and
 // 20.0 us, 24^3 x 48 129 and 117, 32^3 x 64 399 and 364; both parities, 12-real:
-// 41.4 and 36.5, 216 and 223, 757 and 701.  The other formats, which encode
-// each neighbour eight times, only while the call is bound by its launches:
-// FP32 and FP16, one parity: 20^4 21.9 and 17.9, 20.2 and 18.8, 24^4 35.3 and
-// 35.8, 31.1 and 36.8; both: 12^3 x 24 13.4 and 11.8, 16^4 18.1 and 18.4, 16.1
-// and 18.5.
+// 41.4 and 36.5, 216 and 223, 757 and 701 (of these the copy wins 3 % at 24^3 x
+// 48, which is not worth a line of its own and a workspace of the whole field).
+// The other formats, which encode each neighbour eight times, only while the
+// call is bound by its launches: FP32 and FP16, one parity: 20^4 21.9 and 17.9,
+// 20.2 and 18.8, 24^4 35.3 and 35.8, 31.1 and 36.8; both: 12^3 x 24 13.4 and
+// 11.8, 16^4 18.1 and 18.4, 16.1 and 18.5.
 bool op_reads_canonical(const wd_ctx *c, int sp, int np, const void *in, const void *out, size_t in_bytes,
                         size_t out_bytes)
 {

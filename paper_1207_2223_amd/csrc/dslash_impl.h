@@ -21,8 +21,6 @@
 //              directions of several iterations at once, by the p update).
 //              With r's source another field and alpha = 1 it forms the true
 //              residual r = b - Ap of a reliable update.
-//              With r's source another field and alpha = 1 it forms the true
-//              residual r = b - Ap of a reliable update.
 // Partial sums cover 16 consecutive sites of one RHS and are formed with the
 // same pairing tree for every (NR, RL, block) choice, so every launch shape
 // gives bitwise-identical vectors and norms.
@@ -898,8 +896,8 @@ __global__ void __launch_bounds__(256) dslash_tw_kernel(DslashArgs a)
 #pragma unroll
             for (int e = 0; e < 24; e++) acc[r][e] = 0;
         // (every site is live; the test keeps the hops in a region of their
-        // own, as in dslash_kernel, which the compiler schedules with far
-        // fewer registers than the same code without it)
+        // own, which the compiler schedules with far fewer registers than the
+        // same code without it)
         const bool live = i < b.g.Vh;
         if (live) {
             int c[4];

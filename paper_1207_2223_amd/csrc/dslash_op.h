@@ -14,10 +14,6 @@
 
 namespace wd {
 
-// A complex number of the caller's field: the interface asks for doubles, so
-// only their alignment is taken for granted.
-typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
-
 // Source of the terms' spinors: the canonical complex128 field, 24 consecutive
 // doubles a site.  full: lex order of the whole lattice (site 2 * cb + the low
 // bit of x), else the cb order of one parity.  A neighbour is encoded to the

@@ -75,7 +75,6 @@ __device__ __forceinline__ M3 mul_dag(const M3 &a, const M3 &b)
 // factor from LDS.
 constexpr int kRowLinks = 21;
 constexpr int kRowWords = (kRowLinks + 1) * 9;  // (lane 63 has no link: it reads the unused last one)
-typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
 
 struct Row3 {
     double2 e[3];

@@ -2,16 +2,16 @@
 // cannot allocate device memory (code under HIP graph capture, tight serving
 // loops, harnesses that forbid it).
 //
-// The packed operand and the two temporaries of the sweeps that wd_mdagm keeps
-// in context workspaces live here in one file-scope device array, `scratch`, of kScratchBytes per GPU (held by each
-// GPU the library runs on until the process ends).  Its device address is
-// looked up once per device with hipGetSymbolAddress, with that device
-// current, when the first context on that device is created (wd_create), and
-// only that address is handed to kernels.  The entry point itself calls no
-// allocating routine and no host-device copy.  Every call on one GPU uses that GPU's array, so calls
-// that overlap on one GPU (different streams or threads) race; the array
-// keeps the last call's contents, and nothing in it is read before this call
-// has written it.
+// The temporaries of the sweeps that wd_mdagm keeps in context workspaces live
+// here in one file-scope device array, `scratch`, of kScratchBytes per GPU
+// (held by each GPU the library runs on until the process ends).  Its device
+// address is looked up once per device with hipGetSymbolAddress, with that
+// device current, when the first context on that device is created
+// (wd_create), and only that address is handed to kernels.  The entry point
+// itself calls no allocating routine and no host-device copy.  Every call on
+// one GPU uses that GPU's array, so calls that overlap on one GPU (different
+// streams or threads) race; the array keeps the last call's contents, and
+// nothing in it is read before this call has written it.
 #include <cmath>
 #include <mutex>
 
@@ -63,8 +63,9 @@ extern "C" wd_status wd_mdagm_noalloc(wd_ctx *c, double *out, const double *in, 
     if (!std::isfinite(kappa)) return set_error(WD_ERR_ARG, "kappa not finite");
     char *base = (char *)scratch_ptr(c->device);
     if (!base) return set_error(WD_ERR_STATE, "no device scratch on device %d (context not from wd_create?)", c->device);
-    // temporaries T and B of wd_mdagm, and the limit that callers know: 6
-    // subfields for the full operator, 4 for the even-odd one
+    // the limit that callers know: 6 subfields for the full operator, 4 for the
+    // even-odd one (what wd_mdagm took when it packed its operand; T and B take
+    // 2 and 3, but a lattice that is refused stays refused)
     const long long sub = ((long long)spinor_site_bytes(SP_F64) * c->g.cs + 255) / 256 * 256;
     const size_t need = kHeadBytes + (size_t)((eo ? 4 : 6) * sub);
     if (need > kScratchBytes)

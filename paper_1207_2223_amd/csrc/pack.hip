@@ -25,10 +25,6 @@ __device__ __forceinline__ void lex_to_eo(const Geom &g, long long lex, int *P, 
     *cb = (int)(lex >> 1);
 }
 
-// A complex number of the caller's field (only the alignment of doubles is
-// taken for granted).
-typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
-
 // Links: all the packed formats in one pass over the canonical field.  A
 // work-group stages 64 consecutive sites (36 KB, read as they lie) in LDS;
 // wave mu then takes direction mu, its lanes 0-31 the even and 32-63 the odd
@@ -273,8 +269,6 @@ hipError_t debug_tables(const Geom &g, int32_t *nb, int32_t *cb, uint8_t *par, h
 // memory.  (One site a thread, 192-byte strides: 54 us for one column at 16^3 x
 // 32, 9.3 now; twelve columns of 16^4 16.8 each, 47.8 in one launch, 6.3 TB/s.)
 namespace {
-typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
-
 __global__ void __launch_bounds__(256) k_merge(const double *e, const double *o, double so, double *full, Geom g)
 {
     const unsigned w = blockIdx.x * 256u + threadIdx.x, x = w / 12u;
@@ -287,12 +281,12 @@ __global__ void __launch_bounds__(256) k_merge(const double *e, const double *o,
     const unsigned P = (c0 + c1 + r % (unsigned)g.L[2] + r / (unsigned)g.L[2]) & 1u;
     const size_t col = (size_t)blockIdx.y * (size_t)g.Vh * 24;
     const size_t k = (size_t)(x >> 1) * 24 + 2 * (w - 12u * x);
-    pair_t v = *reinterpret_cast<const pair_t *>((P ? o : e) + col + k);
+    dbl2u_t v = *reinterpret_cast<const dbl2u_t *>((P ? o : e) + col + k);
     if (P) {
         v.x *= so;
         v.y *= so;
     }
-    *reinterpret_cast<pair_t *>(full + 2 * col + 2 * (size_t)w) = v;
+    *reinterpret_cast<dbl2u_t *>(full + 2 * col + 2 * (size_t)w) = v;
 }
 }  // namespace
 

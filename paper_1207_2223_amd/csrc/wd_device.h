@@ -163,6 +163,9 @@ __device__ __forceinline__ int neighbour(const Geom &g, int i, const int c[4])
 // marked so that the L2 keeps the neighbour spinors and links, which are
 // read by up to eight sites.  The hint changes caching only, never values.
 typedef double dbl2_t __attribute__((ext_vector_type(2)));
+// A complex number of the caller's field: the interface asks for doubles, so
+// only their alignment is taken for granted.
+typedef double dbl2u_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float flt4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
